@@ -127,22 +127,38 @@ __device__ __forceinline__ double dpp_f64(double v) {
     return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-/* Lane exchanges of the row reductions, in the order they are applied: lanes 32 apart, 16 apart,
-   mirrored inside each 16-lane row (i <-> 15 - i), then the two quad swaps and the mirror inside
-   each 8-lane half.  Each step pairs every lane with one partner, and together they join all 64. */
 /* The six exchanges of a wave reduction, in the order every reduction here uses.  Level k pairs
    lane l with a partner that differs from l in lane bit 5 - k, and before level k every lane
    differing from l only in lower bits holds the same set of partial sums, so the extra low bits
    flipped by the mirrors do not matter: level 0 l ^ 32, level 1 l ^ 16, level 2 the row mirror
-   (l ^ 15), level 3 the half-row mirror (l ^ 7), level 4 l ^ 2, level 5 l ^ 1. */
+   (l ^ 15), level 3 the half-row mirror (l ^ 7), level 4 l ^ 2, level 5 l ^ 1.  Together they join
+   all 64 lanes. */
+
+/* Levels 0 and 1 are lane swaps: the upper half of a (of each pair of 16-lane rows) changes places
+   with the lower half of b, after which a + b is, lane by lane, the sum of a's two halves below and
+   of b's two halves above.  One swap and one addition thus do a transposed step on two entries,
+   where an exchange through LDS took two selects, the LDS round trip and the addition. */
 template <int LEVEL>
-__device__ __forceinline__ float xchg(float v) {
-    if constexpr (LEVEL == 0) return __shfl_xor(v, 32);
-    else if constexpr (LEVEL == 1) return __shfl_xor(v, 16);
-    else if constexpr (LEVEL == 2) return dpp_f32<DPP_MIRROR>(v);
-    else if constexpr (LEVEL == 3) return dpp_f32<DPP_HALF_MIRROR>(v);
-    else if constexpr (LEVEL == 4) return dpp_f32<DPP_XOR2>(v);
-    else return dpp_f32<DPP_XOR1>(v);
+__device__ __forceinline__ float swap_add(float a, float b) {
+    static_assert(LEVEL < 2, "levels 0 and 1");
+    const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    if constexpr (LEVEL == 0) {
+        const auto s = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    } else {
+        const auto s = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+}
+
+/* v plus the partner's v. */
+template <int LEVEL>
+__device__ __forceinline__ float xchg_add(float v) {
+    if constexpr (LEVEL < 2) return swap_add<LEVEL>(v, v);
+    else if constexpr (LEVEL == 2) return v + dpp_f32<DPP_MIRROR>(v);
+    else if constexpr (LEVEL == 3) return v + dpp_f32<DPP_HALF_MIRROR>(v);
+    else if constexpr (LEVEL == 4) return v + dpp_f32<DPP_XOR2>(v);
+    else return v + dpp_f32<DPP_XOR1>(v);
 }
 
 /* One transposed step: lanes whose `bit` is set keep the upper half of the row list and send the
@@ -153,9 +169,16 @@ __device__ __forceinline__ void halve_rows(float (&a)[N], int n, bool upper) {
 #pragma unroll
     for (int j = 0; j < N / 2; ++j) {
         if (j < h) {
-            const float send = upper ? a[j] : a[j + h];
-            const float keep = upper ? a[j + h] : a[j];
-            a[j] = keep + xchg<LEVEL>(send);
+            if constexpr (LEVEL < 2) {
+                a[j] = swap_add<LEVEL>(a[j], a[j + h]);
+            } else {
+                const float send = upper ? a[j] : a[j + h];
+                const float keep = upper ? a[j + h] : a[j];
+                if constexpr (LEVEL == 2) a[j] = keep + dpp_f32<DPP_MIRROR>(send);
+                else if constexpr (LEVEL == 3) a[j] = keep + dpp_f32<DPP_HALF_MIRROR>(send);
+                else if constexpr (LEVEL == 4) a[j] = keep + dpp_f32<DPP_XOR2>(send);
+                else a[j] = keep + dpp_f32<DPP_XOR1>(send);
+            }
         }
     }
 }
@@ -182,12 +205,12 @@ __device__ __forceinline__ void wave_sum_entries(float (&a)[N], int lane) {
     halve_level<3, N>(a, lane);
     halve_level<4, N>(a, lane);
     halve_level<5, N>(a, lane);
-    if constexpr (N < 2) a[0] += xchg<0>(a[0]);
-    if constexpr (N < 4) a[0] += xchg<1>(a[0]);
-    if constexpr (N < 8) a[0] += xchg<2>(a[0]);
-    if constexpr (N < 16) a[0] += xchg<3>(a[0]);
-    if constexpr (N < 32) a[0] += xchg<4>(a[0]);
-    if constexpr (N < 64) a[0] += xchg<5>(a[0]);
+    if constexpr (N < 2) a[0] = xchg_add<0>(a[0]);
+    if constexpr (N < 4) a[0] = xchg_add<1>(a[0]);
+    if constexpr (N < 8) a[0] = xchg_add<2>(a[0]);
+    if constexpr (N < 16) a[0] = xchg_add<3>(a[0]);
+    if constexpr (N < 32) a[0] = xchg_add<4>(a[0]);
+    if constexpr (N < 64) a[0] = xchg_add<5>(a[0]);
 }
 
 template <int N>
