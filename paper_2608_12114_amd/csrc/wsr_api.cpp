@@ -427,6 +427,9 @@ wsr_status plan_table(const wsr_mat* mats, int32_t n, int32_t batch, int32_t n_t
     /* Passes of `batch` tokens, at most 8 when the table holds q4 or int8 matrices. */
     for (int32_t i = 0; i < n && batch > 8; ++i)
         if (mats[i].fmt == WSR_Q4 || mats[i].fmt == WSR_I8) batch = 8;
+    /* Rows too long for the multi-column kernels: token by token, the same bits. */
+    for (const DevMat& d : p.tab)
+        if (d.nc > wsr::COLS_MAX_NC) batch = 1;
     p.batch = batch;
     return ok();
 }
@@ -443,7 +446,7 @@ wsr_status run_sweep(const SweepPlan& p, int32_t n, int32_t n_tokens, void* ws, 
     bool upload = false;
     for (int32_t t = 0, T = p.batch; t < n_tokens && !upload; t += T) {
         while (T > n_tokens - t) T >>= 1;
-        for (const Seg& g : p.segs) upload |= !wsr::sweep_table_by_value(g.count, g.total, g.fmt, T);
+        for (const Seg& g : p.segs) upload |= !wsr::sweep_table_by_value(p.tab.data() + g.first, g.count, g.total, g.fmt, T);
     }
     hipError_t e = hipSuccess;
     if (upload && (e = wsr::launch_put_table(dtab, dcost, p.tab.data(), n, ctr, s)) != hipSuccess)
@@ -885,7 +888,7 @@ extern "C" wsr_status wsr_decode_sweep_mma(const wsr_mat* mats, int32_t n, int32
     bool upload = false;
     for (int32_t t = 0; t < n_tokens && !upload; t += 16)
         for (const Seg& g : p.segs)
-            upload |= std::min<int32_t>(16, n_tokens - t) > 1 || !wsr::sweep_table_by_value(g.count, g.total, g.fmt, 1);
+            upload |= std::min<int32_t>(16, n_tokens - t) > 1 || !wsr::sweep_table_by_value(p.tab.data() + g.first, g.count, g.total, g.fmt, 1);
     hipError_t e = hipSuccess;
     if (upload && (e = wsr::launch_put_table(dtab, dcost, p.tab.data(), n, ctr, s)) != hipSuccess)
         return hip_fail(e, "decode_sweep_mma: table upload");

@@ -337,34 +337,17 @@ __device__ __forceinline__ void group16_cols(const char* W, g_u32x4* x, int64_t 
                 for (int u = 0; u < U; ++u) acc[t * R + r] = dot8<FMT>(wv[r][u], xv[t][u], acc[t * R + r]);
     }
     wave_sum_entries<N>(acc, lane);
-    if constexpr (N <= WAVE) {
-        if ((lane & (WAVE / N - 1)) == 0) {
-            const int e = lane / (WAVE / N);
-            y[(e / R) * ycs + i + e % R] = acc[0];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < N / WAVE; ++j) {
-            const int e = lane * (N / WAVE) + j;
-            y[(e / R) * ycs + i + e % R] = acc[j];
-        }
+    static_assert(N <= WAVE, "one total per lane");
+    if ((lane & (WAVE / N - 1)) == 0) {
+        const int e = lane / (WAVE / N);
+        y[(e / R) * ycs + i + e % R] = acc[0];
     }
 }
 
-/* Launch shape of the multi-column 16-bit row loops: rows per wave R and chunks per lane per step U
-   for T columns.  A step loads R U weight chunks and T U activation chunks per lane, so tall row
-   groups keep the activation reloads (from L2) below the weight stream; measured on the 70B
-   sweep, these shapes hold the weight stream at 7.1, 6.9, 6.5 and 4.6 TB/s for T = 2, 4, 8, 16. */
-template <int T> struct Cols16 { static constexpr int R = 1, U = 8; };
-template <> struct Cols16<2> { static constexpr int R = 4, U = 4; };
-template <> struct Cols16<4> { static constexpr int R = 8, U = 1; };
-template <> struct Cols16<8> { static constexpr int R = 16, U = 1; };
-template <> struct Cols16<16> { static constexpr int R = 8, U = 1; };
-
-/* Rows [r0, r1) of matrix d for tokens token0 .. token0 + T - 1 in one pass over the weights. */
-template <int FMT, int T, int R = Cols16<T>::R, int U = Cols16<T>::U>
-__device__ __forceinline__ void rows16_cols(const DevMat& d, int64_t r0, int64_t r1, int32_t token0,
-                                            int lane) {
+/* Rows [r0, r1) of a 16-bit matrix for tokens token0 .. token0 + T - 1: groups of R rows, then one at a
+   time. */
+template <int FMT, int R, int U, int T>
+__device__ __forceinline__ void rows16_cols(const DevMat& d, int64_t r0, int64_t r1, int32_t token0, int lane) {
     const char* W = static_cast<const char*>(d.w);
     g_u32x4* x = as_global<g_u32x4*>(static_cast<const char*>(d.x) + token0 * d.x_stride);
     g_f32* y = as_global<g_f32*>(reinterpret_cast<char*>(d.y) + token0 * d.y_stride);
@@ -542,110 +525,6 @@ __device__ __forceinline__ void q4_group(g_u32x4* Wq, g_u16* S, g_u32x4* x, g_f3
     q4_store<R>(y, i, acc, lane);
 }
 
-/* Rows [i, i + R) of a q4 matrix against T activation columns in one pass over the codes: each
-   row's block is decoded once per step and dotted with every column's activation pairs.  Per
-   (row, column) the arithmetic and its order are those of q4_block_dot and q4_store, and the
-   R * T totals share the reduction tree, so each column equals the single-column result bit for
-   bit.  Column t of x starts xcs 16-byte chunks after column 0, its outputs ycs floats after. */
-template <int R, int T>
-__device__ __forceinline__ void q4_group_cols(g_u32x4* Wq, g_u16* S, g_u32x4* x, int64_t xcs, g_f32* y,
-                                              int64_t ycs, int64_t nb, int64_t i, int lane) {
-    constexpr int N = R * T;
-    float acc[N];                                   /* entry t * R + r */
-#pragma unroll
-    for (int e = 0; e < N; ++e) acc[e] = 0.f;
-    g_u32x4* wr[R];
-    g_u16* sr[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        wr[r] = Wq + (i + r) * nb;
-        sr[r] = S + (i + r) * nb;
-    }
-    for (int64_t b0 = 0; b0 < nb; b0 += WAVE) {
-        const int64_t b = b0 + lane;
-        const bool ok = b < nb;
-        u32x4 xv[T][4], wv[R];
-        uint16_t sv[R];
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) xv[t][j] = ok ? load_reused(x + t * xcs + 4 * b + j) : zero4();
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            wv[r] = ok ? load_once(wr[r] + b) : zero4();
-            sv[r] = ok ? sr[r][b] : (uint16_t)0;
-        }
-        uint32_t dec[R][16];                        /* decoded subnormal pairs, q4_block_dot's order */
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const uint32_t wd[4] = {wv[r].x, wv[r].y, wv[r].z, wv[r].w};
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint32_t w0 = wd[d], w8 = wd[d] >> 8;
-                dec[r][4 * d + 0] = (w0 ^ Q4_SIGN) & Q4_LO;
-                dec[r][4 * d + 1] = (w0 ^ Q4_SIGN) & Q4_HI;
-                dec[r][4 * d + 2] = (w8 ^ Q4_SIGN) & Q4_LO;
-                dec[r][4 * d + 3] = (w8 ^ Q4_SIGN) & Q4_HI;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            Q4X q;
-            q4_prep(xv[t], q);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float se = 0.f, so = 0.f;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    se = dot2<FMT_F16>(dec[r][4 * d + 0], q.p[4 * d + 0], se);
-                    so = dot2<FMT_F16>(dec[r][4 * d + 1], q.p[4 * d + 1], so);
-                    se = dot2<FMT_F16>(dec[r][4 * d + 2], q.p[4 * d + 2], se);
-                    so = dot2<FMT_F16>(dec[r][4 * d + 3], q.p[4 * d + 3], so);
-                }
-                const float blk = __builtin_fmaf(so, 0.0625f, se) - q.off;
-                acc[t * R + r] = __builtin_fmaf(f16_bits_to_f32(sv[r]), blk, acc[t * R + r]);
-            }
-        }
-    }
-    wave_sum_entries<N>(acc, lane);
-    if constexpr (N <= WAVE) {
-        if ((lane & (WAVE / N - 1)) == 0) {
-            const int e = lane / (WAVE / N);
-            y[(e / R) * ycs + i + e % R] = acc[0] * 16777216.0f;   /* undo the 2^-24 unit (exact) */
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < N / WAVE; ++j) {
-            const int e = lane * (N / WAVE) + j;
-            y[(e / R) * ycs + i + e % R] = acc[j] * 16777216.0f;
-        }
-    }
-}
-
-/* Rows per wave of the multi-column q4 loop for T = 1, 2, 4, 8 columns (the T raw activation
-   blocks and R decoded rows stay in registers, so T stops at 8).  A 16-byte code block needs 64
-   bytes of activations per column, so a step reloads 4 T / R activation bytes (from L2) per code
-   byte; with registers for only R T sums, that traffic, not HBM, sets the rate of these passes. */
-template <int T> struct Cols4 { static constexpr int R = 8; };
-template <> struct Cols4<2> { static constexpr int R = 4; };
-template <> struct Cols4<4> { static constexpr int R = 4; };
-template <> struct Cols4<8> { static constexpr int R = 2; };
-
-/* Rows [r0, r1) of a q4 matrix for tokens token0 .. token0 + T - 1 in one pass over the codes. */
-template <int T, int R = Cols4<T>::R>
-__device__ __forceinline__ void rows_q4_cols(const DevMat& d, int64_t r0, int64_t r1, int32_t token0,
-                                             int lane) {
-    static_assert(T <= 8, "q4 takes at most 8 columns per pass");
-    g_u32x4* Wq = as_global<g_u32x4*>(d.w);
-    g_u16* S = as_global<g_u16*>(d.s);
-    g_u32x4* x = as_global<g_u32x4*>(static_cast<const char*>(d.x) + token0 * d.x_stride);
-    g_f32* y = as_global<g_f32*>(reinterpret_cast<char*>(d.y) + token0 * d.y_stride);
-    const int64_t xcs = d.x_stride / 16, ycs = d.y_stride / 4;
-    int64_t i = r0;
-    for (; i + R <= r1; i += R) q4_group_cols<R, T>(Wq, S, x, xcs, y, ycs, d.nc, i, lane);
-    for (; i < r1; ++i) q4_group_cols<1, T>(Wq, S, x, xcs, y, ycs, d.nc, i, lane);
-}
-
 /* ---- int8 rows with fp16 row scales -------------------------------------------------------------
 
    The paper's protocol format (Sec. 3.1): w[i,k] = q[i,k] * s[i], q two's-complement int8, one fp16
@@ -692,19 +571,19 @@ __device__ __forceinline__ float i8_chunk_dot(u32x4 w, const I8X& q) {
     return t - q.off;
 }
 
-/* Rows [i, i + R) of an int8 matrix against T activation columns (T = 1: a single GEMV) in one
-   pass over the codes.  Column t of x starts xcs 16-byte chunks after column 0 (two chunks of x
-   per chunk of codes), its outputs ycs floats after.  Every (row, column) sum follows the same
-   chunk sequence and reduction tree whatever R, U and T are, so results do not depend on them. */
+/* Rows [i, i + R) of an int8 matrix against T activation columns (1 or 2), one step at a time.  Column
+   t of x starts xcs 16-byte chunks after column 0 (two chunks of x per chunk of codes), its outputs
+   ycs floats after.  Every (row, column) sum follows the same chunk sequence and reduction tree
+   whatever R, U and T are, so results do not depend on them. */
 template <int R, int U, int T>
 __device__ __forceinline__ void group_i8(g_u32x4* Wq, const uint16_t* S, g_u32x4* x, int64_t xcs, g_f32* y,
                                          int64_t ycs, int64_t nc, int64_t i, int lane) {
     constexpr int STEP = WAVE * U;
     constexpr int N = R * T;
     float acc[N];                                   /* entry t * R + r */
+    g_u32x4* wr[R];
 #pragma unroll
     for (int e = 0; e < N; ++e) acc[e] = 0.f;
-    g_u32x4* wr[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) wr[r] = Wq + (i + r) * nc;
     for (int64_t c0 = 0; c0 < nc; c0 += STEP) {
@@ -732,42 +611,33 @@ __device__ __forceinline__ void group_i8(g_u32x4* Wq, const uint16_t* S, g_u32x4
             }
     }
     wave_sum_entries<N>(acc, lane);
-    auto out = [&](int e, float v) {
-        const float rs = f16_bits_to_f32(S[i + e % R]);
-        y[(e / R) * ycs + i + e % R] = v * 16777216.0f * rs;   /* 2^24 exact, then the row scale */
-    };
-    if constexpr (N <= WAVE) {
-        if ((lane & (WAVE / N - 1)) == 0) out(lane / (WAVE / N), acc[0]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < N / WAVE; ++j) out(lane * (N / WAVE) + j, acc[j]);
+    if ((lane & (WAVE / N - 1)) == 0) {
+        const int e = lane / (WAVE / N);
+        const int64_t row = i + e % R;
+        y[(e / R) * ycs + row] = acc[0] * 16777216.0f * f16_bits_to_f32(S[row]);   /* 2^24 exact, then the row scale */
     }
 }
 
-/* Rows per wave and chunks per lane per step of the int8 sweep loops for T columns (T <= 8): eight
-   rows share each activation chunk's preparation, one chunk per lane per step keeps the register
-   count low enough for several waves per SIMD. */
-template <int T> struct ColsI8 { static constexpr int R = 8, U = 1; };
-/* The same for the standalone int8 GEMV kernels (one group of R rows per wave). */
-template <int T> struct GemvI8 { static constexpr int R = 4, U = 1; };
-template <> struct GemvI8<2> { static constexpr int R = 4, U = 2; };
-template <> struct GemvI8<4> { static constexpr int R = 8, U = 1; };
-template <> struct GemvI8<8> { static constexpr int R = 8, U = 1; };
-/* Register sets in flight in the single-column int8 row loop. */
+/* Rows per wave of the int8 sweep: eight share each activation chunk's preparation, one chunk per lane
+   per step keeps the register count low enough for several waves per SIMD. */
+constexpr int I8_R = 8;
+/* The same for the standalone int8 GEMV (one group of rows per wave). */
+constexpr int I8_GEMV_R = 4;
+/* Register sets in flight in the int8 row loop. */
 constexpr int I8_NB = 3;
 
-/* Rows [r0, r1) of an int8 matrix for tokens token0 .. token0 + T - 1 in one pass over the codes. */
-template <int T, int R = ColsI8<T>::R, int U = ColsI8<T>::U>
-__device__ __forceinline__ void rows_i8(const DevMat& d, int64_t r0, int64_t r1, int32_t token0, int lane) {
-    static_assert(T <= 8, "int8 takes at most 8 columns per pass");
+/* Rows [r0, r1) of an int8 matrix for tokens token .. token + T - 1: groups of R rows, then one at a
+   time. */
+template <int R, int T = 1>
+__device__ __forceinline__ void rows_i8(const DevMat& d, int64_t r0, int64_t r1, int32_t token, int lane) {
     g_u32x4* Wq = as_global<g_u32x4*>(d.w);
     const uint16_t* S = static_cast<const uint16_t*>(d.s);
-    g_u32x4* x = as_global<g_u32x4*>(static_cast<const char*>(d.x) + token0 * d.x_stride);
-    g_f32* y = as_global<g_f32*>(reinterpret_cast<char*>(d.y) + token0 * d.y_stride);
-    const int64_t xcs = d.x_stride / 16, ycs = d.y_stride / 4;
+    g_u32x4* x = as_global<g_u32x4*>(static_cast<const char*>(d.x) + token * d.x_stride);
+    g_f32* y = as_global<g_f32*>(reinterpret_cast<char*>(d.y) + token * d.y_stride);
     int64_t i = r0;
-    for (; i + R <= r1; i += R) group_i8<R, U, T>(Wq, S, x, xcs, y, ycs, d.nc, i, lane);
-    for (; i < r1; ++i) group_i8<1, U, T>(Wq, S, x, xcs, y, ycs, d.nc, i, lane);
+    const int64_t xcs = d.x_stride / 16, ycs = d.y_stride / 4;
+    for (; i + R <= r1; i += R) group_i8<R, 1, T>(Wq, S, x, xcs, y, ycs, d.nc, i, lane);
+    for (; i < r1; ++i) group_i8<1, 1, T>(Wq, S, x, xcs, y, ycs, d.nc, i, lane);
 }
 
 /* One step of the int8 row loop: R rows x U chunks of codes and the U activation chunk pairs. */
@@ -781,7 +651,7 @@ struct I8Step {
    (group of R rows, step) is decoded the loads of the next NB - 1 units are outstanding, across
    row-group boundaries, as in the q4 loop below.  Needs rows made of whole steps (nc a multiple of
    64 U); otherwise, and for the rows left over, group_i8 runs.  Every sum takes the chunks and
-   the reduction tree of group_i8, so the results are those of rows_i8<1>. */
+   the reduction tree of group_i8, so the results are those of rows_i8. */
 template <int R, int U, int NB>
 __device__ __forceinline__ void rows_i8_pipe(const DevMat& d, int64_t r0, int64_t r1, int32_t token, int lane) {
     g_u32x4* Wq = as_global<g_u32x4*>(d.w);
@@ -968,8 +838,9 @@ __device__ __forceinline__ int first_matrix(const int64_t* __restrict__ cost, in
 }
 
 
-template <int FMT, int R16, int U16, int RQ, int UQ, int QNB = 2, int T = 1, int RC = Cols16<T>::R,
-          int UC = Cols16<T>::U, int RQC = Cols4<(T <= 8 ? T : 8)>::R>
+/* The rows of the byte range [lo, hi) of the weight stream, at token `token` (int8: T = 2 takes tokens
+   token and token + 1 together). */
+template <int FMT, int R16, int U16, int RQ, int UQ, int T = 1>
 __device__ __forceinline__ void stream_range(const DevMat* __restrict__ tab, const int64_t* __restrict__ cost,
                                              int nmat, int64_t lo, int64_t hi, int32_t token, int lane,
                                              int& hint) {
@@ -978,32 +849,21 @@ __device__ __forceinline__ void stream_range(const DevMat* __restrict__ tab, con
         if (d.cost0 >= hi) break;
         hint = m;
         const int fmt = FMT ? FMT : d.fmt;
-        const int64_t g = fmt == FMT_Q4 ? (T == 1 ? RQ : RQC)
-                        : fmt == FMT_I8 ? ColsI8<(T <= 8 ? T : 8)>::R
-                                        : (T == 1 ? R16 : RC);
+        const int64_t g = fmt == FMT_Q4 ? RQ : fmt == FMT_I8 ? I8_R : R16;
         /* a byte range maps to rows by rounding both ends up to the next group of g rows */
         const int64_t r0 = lo > d.cost0 ? ceil_div(lo - d.cost0, d.row_bytes * g) * g : 0;
         const int64_t e1 = ceil_div(hi - d.cost0, d.row_bytes * g) * g;
         const int64_t r1 = d.M < e1 ? d.M : e1;
         if (r0 >= r1) continue;
-        if constexpr (T == 1) {
-            if ((FMT == 0 || FMT == FMT_F16) && fmt == FMT_F16)
-                rows16<FMT_F16, R16, U16>(d, r0, r1, token, lane);
-            else if ((FMT == 0 || FMT == FMT_BF16) && fmt == FMT_BF16)
-                rows16<FMT_BF16, R16, U16>(d, r0, r1, token, lane);
-            else if ((FMT == 0 || FMT == FMT_Q4) && fmt == FMT_Q4)
-                rows_q4<RQ, UQ, QNB>(d, r0, r1, token, lane);
-            else if ((FMT == 0 || FMT == FMT_I8) && fmt == FMT_I8)
-                rows_i8_pipe<ColsI8<1>::R, ColsI8<1>::U, I8_NB>(d, r0, r1, token, lane);
-        } else {                                        /* tokens token .. token + T - 1 together */
-            if ((FMT == 0 || FMT == FMT_F16) && fmt == FMT_F16)
-                rows16_cols<FMT_F16, T, RC, UC>(d, r0, r1, token, lane);
-            else if ((FMT == 0 || FMT == FMT_BF16) && fmt == FMT_BF16)
-                rows16_cols<FMT_BF16, T, RC, UC>(d, r0, r1, token, lane);
-            else if constexpr (T <= 8) {
-                if ((FMT == 0 || FMT == FMT_Q4) && fmt == FMT_Q4) rows_q4_cols<T, RQC>(d, r0, r1, token, lane);
-                else if ((FMT == 0 || FMT == FMT_I8) && fmt == FMT_I8) rows_i8<T>(d, r0, r1, token, lane);
-            }
+        if ((FMT == 0 || FMT == FMT_F16) && fmt == FMT_F16)
+            rows16<FMT_F16, R16, U16>(d, r0, r1, token, lane);
+        else if ((FMT == 0 || FMT == FMT_BF16) && fmt == FMT_BF16)
+            rows16<FMT_BF16, R16, U16>(d, r0, r1, token, lane);
+        else if ((FMT == 0 || FMT == FMT_Q4) && fmt == FMT_Q4)
+            rows_q4<RQ, UQ>(d, r0, r1, token, lane);
+        else if ((FMT == 0 || FMT == FMT_I8) && fmt == FMT_I8) {
+            if constexpr (T == 1) rows_i8_pipe<I8_R, 1, I8_NB>(d, r0, r1, token, lane);
+            else rows_i8<I8_R, T>(d, r0, r1, token, lane);
         }
     }
 }

@@ -44,12 +44,23 @@ hipError_t launch_put_table(DevMat* dst, int64_t* cost, const DevMat* src, int n
                             hipStream_t s);
 /* One pass over the table's weights for tokens token .. token + T - 1 (T = 1, 2, 4, 8, 16; at most
    8 when the table holds a q4 or int8 matrix).  tab / cost: the table in device memory (written by
-   launch_put_table); htab: the same table on the host, or null.  A launch for which
-   sweep_table_by_value() holds and htab is given carries the table in its arguments and reads
+   launch_put_table); htab: the same table on the host.  A launch for which
+   sweep_table_by_value() holds carries the table in its arguments and reads
    neither tab, cost nor ctr. */
 hipError_t launch_sweep(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total_bytes,
                         int fmt_all, int32_t token, int T, unsigned* ctr, hipStream_t s);
-bool sweep_table_by_value(int nmat, int64_t total_bytes, int fmt_all, int T);
+/* Tokens (or columns) token .. token + T - 1 (2 <= T <= 16, at most 8 with a q4 or int8 matrix) in one
+   pass over the weights, each bit for bit the single-token result.  htab: the table on the host; with
+   at most COLS_TABLE_ARG matrices it goes by value, else the kernels read tab and cost.  Every nc is
+   at most COLS_MAX_NC: the kernels address sixteen rows with 32-bit offsets (rows of up to 256 MiB;
+   the callers take longer rows column by column, whose results are the same bits). */
+constexpr int COLS_TABLE_ARG = 8;
+constexpr int64_t COLS_MAX_NC = (int64_t{1} << 24) - 1;
+hipError_t launch_cols(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total_bytes,
+                       int fmt_all, int32_t token, int T, hipStream_t s);
+/* Whether that pass takes the kernel for short streams. */
+bool cols_takes_split(const DevMat* htab, int nmat, int fmt_all, int T);
+bool sweep_table_by_value(const DevMat* htab, int nmat, int64_t total_bytes, int fmt_all, int T);
 
 /* Sweep workspace: tile counters in the first SWEEP_CTR_BYTES, then the table, then the matrices'
    stream offsets (DevMat::cost0) as a dense int64 array, each part padded to 256 bytes. */

@@ -145,78 +145,50 @@ static hipError_t launch_rows(K kernel, const DevMat& m, int R, hipStream_t s) {
     return hipGetLastError();
 }
 
-/* T activation columns per weight read (x_stride / y_stride of d are the column strides). */
-template <int FMT, int T>
-__global__ __launch_bounds__(BLOCK) void k_gemv16_cols(DevMat d) {
-    constexpr int R = Cols16<T>::R;
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
-    const int64_t r0 = wave * R;
-    if (r0 >= d.M) return;
-    rows16_cols<FMT, T>(d, r0, std::min<int64_t>(r0 + R, d.M), 0, lane);
-}
-
-template <int FMT>
-static hipError_t launch_gemv16_cols(const DevMat& m, int T, hipStream_t s) {
-    switch (T) {
-        case 1: return launch_rows(k_gemv16_cols<FMT, 1>, m, Cols16<1>::R, s);
-        case 2: return launch_rows(k_gemv16_cols<FMT, 2>, m, Cols16<2>::R, s);
-        case 4: return launch_rows(k_gemv16_cols<FMT, 4>, m, Cols16<4>::R, s);
-        case 8: return launch_rows(k_gemv16_cols<FMT, 8>, m, Cols16<8>::R, s);
-        case 16: return launch_rows(k_gemv16_cols<FMT, 16>, m, Cols16<16>::R, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-template <int T>
-__global__ __launch_bounds__(BLOCK) void k_gemv_q4_cols(DevMat d) {
-    constexpr int R = Cols4<T>::R;
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
-    const int64_t r0 = wave * R;
-    if (r0 >= d.M) return;
-    rows_q4_cols<T>(d, r0, std::min<int64_t>(r0 + R, d.M), 0, lane);
-}
-
 /* One group of R rows per wave.  The full and the partial group take separate branches rather than
    a clamp of the row end: the clamp's select was miscompiled (the pre-emit peephole dropped the
    instruction that set the select's condition, so the end became r0 + R past the last row). */
-template <int T>
 __global__ __launch_bounds__(BLOCK) void k_gemv_i8(DevMat d) {
-    constexpr int R = GemvI8<T>::R;
+    constexpr int R = I8_GEMV_R;
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
     const int64_t r0 = wave * R;
     if (r0 >= d.M) return;
-    if (d.M - r0 >= R) rows_i8<T, R, GemvI8<T>::U>(d, r0, r0 + R, 0, lane);
-    else rows_i8<T, 1, GemvI8<T>::U>(d, r0, d.M, 0, lane);
+    if (d.M - r0 >= R) rows_i8<R>(d, r0, r0 + R, 0, lane);
+    else rows_i8<1>(d, r0, d.M, 0, lane);
 }
 
-static hipError_t launch_gemv_i8(const DevMat& m, int T, hipStream_t s) {
-    switch (T) {
-        case 1: return launch_rows(k_gemv_i8<1>, m, GemvI8<1>::R, s);
-        case 2: return launch_rows(k_gemv_i8<2>, m, GemvI8<2>::R, s);
-        case 4: return launch_rows(k_gemv_i8<4>, m, GemvI8<4>::R, s);
-        case 8: return launch_rows(k_gemv_i8<8>, m, GemvI8<8>::R, s);
-        default: return hipErrorInvalidValue;
-    }
+/* Two columns of a 16-bit matrix on the vector ALUs, four rows per wave. */
+constexpr int PAIR16_R = 4;
+template <int FMT>
+__global__ __launch_bounds__(BLOCK) void k_gemv16_pair(DevMat d) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t r0 = ((int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block()) * PAIR16_R;
+    if (r0 >= d.M) return;
+    rows16_cols<FMT, PAIR16_R, 4, 2>(d, r0, std::min<int64_t>(r0 + PAIR16_R, d.M), 0, lane);
+}
+
+/* Where a matrix has rows for four waves per SIMD, two columns cost the vector ALUs little and whole
+   rows per wave, with no sums to join, win over the matrix-core form (us, this and that: 20,000 x
+   1,024 f16 8.1 and 10.5, 20,000 x 4,096 27.4 and 29.2, 100,000 x 4,096 bf16 121 and 128; 8,192 x
+   8,192 29.8 and 25.2). */
+static bool gemv16_pair(const DevMat& m, int T) {
+    return T == 2 && (m.fmt == FMT_F16 || m.fmt == FMT_BF16) && m.M >= 4 * 4 * 1024;
 }
 
 hipError_t launch_gemv_cols(const DevMat& m, int T, hipStream_t s) {
-    if (m.M == 0) return hipSuccess;
-    if (m.fmt == FMT_F16) return launch_gemv16_cols<FMT_F16>(m, T, s);
-    if (m.fmt == FMT_BF16) return launch_gemv16_cols<FMT_BF16>(m, T, s);
-    if (m.fmt == FMT_I8) return launch_gemv_i8(m, T, s);
-    if (m.fmt == FMT_Q4) {
-        switch (T) {
-            case 1: return launch_rows(k_gemv_q4_cols<1>, m, Cols4<1>::R, s);
-            case 2: return launch_rows(k_gemv_q4_cols<2>, m, Cols4<2>::R, s);
-            case 4: return launch_rows(k_gemv_q4_cols<4>, m, Cols4<4>::R, s);
-            case 8: return launch_rows(k_gemv_q4_cols<8>, m, Cols4<8>::R, s);
-            default: return hipErrorInvalidValue;
-        }
+    if (gemv16_pair(m, T))
+        return m.fmt == FMT_F16 ? launch_rows(k_gemv16_pair<FMT_F16>, m, PAIR16_R, s)
+                                : launch_rows(k_gemv16_pair<FMT_BF16>, m, PAIR16_R, s);
+    if (T > 1 && m.nc <= COLS_MAX_NC) return launch_cols(nullptr, nullptr, &m, 1, m.M * m.row_bytes, m.fmt, 0, T, s);
+    DevMat d = m;                                   /* one column, or rows too long: column by column */
+    for (int t = 0; t < T; ++t) {
+        const hipError_t e = launch_gemv(d, s);
+        if (e != hipSuccess) return e;
+        d.x = static_cast<const char*>(d.x) + m.x_stride;
+        d.y = reinterpret_cast<float*>(reinterpret_cast<char*>(d.y) + m.y_stride);
     }
-    return hipErrorInvalidValue;
+    return hipSuccess;
 }
 
 /* Rows of 128 KiB or more (K >= 65536 at 16 bits) go four to a wave when that still leaves a wave
@@ -239,7 +211,7 @@ hipError_t launch_gemv(const DevMat& m, hipStream_t s) {
             return m.nc >= 256 ? launch_rows(k_gemv_q4<2, 2>, m, 2, s)
                                : launch_rows(k_gemv_q4<4, 1>, m, 4, s);
         case FMT_I8:
-            return launch_gemv_i8(m, 1, s);
+            return launch_rows(k_gemv_i8, m, I8_GEMV_R, s);
         default:
             return hipErrorInvalidValue;
     }
@@ -282,7 +254,7 @@ hipError_t launch_put_table(DevMat* dst, int64_t* cost, const DevMat* src, int n
     return hipSuccess;
 }
 
-enum : int { SCHED_TILES = 0, SCHED_SPANS = 1, SCHED_HYBRID = 2 };
+enum : int { SCHED_TILES = 0, SCHED_SPANS = 1 };
 
 /* Tile size: about four tiles per wave, a power of two between 64 KiB and 2 MiB. */
 int64_t sweep_tile(int64_t total, int64_t waves) {
@@ -315,43 +287,32 @@ __device__ __forceinline__ void span_bounds(int64_t total, int64_t w, int64_t sp
      SCHED_TILES   tiles of `tile` bytes, claimed in order from a counter;
      SCHED_SPANS   wave w takes [span w, span (w + 1)) (span = ceil(total / nw)); with many more blocks than the
                    chip holds at once, the hardware starts each block as an earlier one retires,
-                   which balances the end of the token at no cost;
-     SCHED_HYBRID  wave w first takes [span w, span (w + 1)), then the rest [span nw, total) goes out
-                   in claimed tiles, so long uninterrupted runs carry most of the stream and the
-                   waves that finish early share the remainder.
+                   which balances the end of the token at no cost.
    The counters ctr[0] (next tile) and ctr[1] (waves done) start at zero and the last wave to
    finish puts them back to zero for the next launch. */
-template <int FMT, int SCHED, int R16, int U16, int RQ, int UQ, int QNB = 2, int T = 1, int RC = Cols16<T>::R,
-          int UC = Cols16<T>::U, int RQC = Cols4<(T <= 8 ? T : 8)>::R>
+template <int FMT, int SCHED, int R16, int U16, int RQ, int UQ, int T = 1>
 __global__ __launch_bounds__(BLOCK) void k_sweep(const DevMat* __restrict__ tab, const int64_t* __restrict__ cost,
                                                  int nmat, int64_t total, int64_t span, int64_t tile,
                                                  int32_t token, unsigned* __restrict__ ctr) {
     const int lane = threadIdx.x & (WAVE - 1);
     const unsigned nw = gridDim.x * WAVES_PER_BLOCK;
-    const int64_t w = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
     int hint = 0;
     if constexpr (SCHED == SCHED_SPANS) {
         int64_t lo, hi;
         span_bounds(total, span_wave(), span, lo, hi);
-        if (lo < hi) stream_range<FMT, R16, U16, RQ, UQ, QNB, T, RC, UC, RQC>(tab, cost, nmat, lo, hi, token, lane, hint);
+        if (lo < hi) stream_range<FMT, R16, U16, RQ, UQ, T>(tab, cost, nmat, lo, hi, token, lane, hint);
     } else {
-        int64_t base = 0;
-        if constexpr (SCHED == SCHED_HYBRID) {
-            base = span * nw;
-            if (span > 0) stream_range<FMT, R16, U16, RQ, UQ, QNB, T, RC, UC, RQC>(tab, cost, nmat, span * w, span * (w + 1),
-                                                                   token, lane, hint);
-        }
         /* Each wave claims its next tile before working on the current one, so the round trip of
            the claim overlaps the current tile's loads. */
-        const int64_t ntiles = ceil_div(total - base, tile);
+        const int64_t ntiles = ceil_div(total, tile);
         unsigned claim = 0;
         if (lane == 0) claim = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (;;) {
             const unsigned t = __builtin_amdgcn_readfirstlane(claim);
             if ((int64_t)t >= ntiles) break;
             if (lane == 0) claim = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int64_t lo = base + (int64_t)t * tile;
-            stream_range<FMT, R16, U16, RQ, UQ, QNB, T, RC, UC, RQC>(tab, cost, nmat, lo, std::min<int64_t>(total, lo + tile),
+            const int64_t lo = (int64_t)t * tile;
+            stream_range<FMT, R16, U16, RQ, UQ, T>(tab, cost, nmat, lo, std::min<int64_t>(total, lo + tile),
                                                      token, lane, hint);
         }
         if (lane == 0) {
@@ -379,14 +340,14 @@ struct TableArg {
 };
 static_assert(sizeof(TableArg<TABLE_ARG_MAX>) + 32 <= 32000, "the by-value table must stay within the checked argument size");
 
-template <int FMT, int R16, int U16, int T, int N>
+template <int FMT, int R16, int U16, int N, int T>
 __global__ __launch_bounds__(BLOCK) void k_sweep_arg(TableArg<N> tb, int nmat, int64_t total, int64_t span,
                                                      int32_t token) {
     const int lane = threadIdx.x & (WAVE - 1);
     int hint = 0;
     int64_t lo, hi;
     span_bounds(total, span_wave(), span, lo, hi);
-    if (lo < hi) stream_range<FMT, R16, U16, 8, 1, 2, T>(tb.m, tb.cost, nmat, lo, hi, token, lane, hint);
+    if (lo < hi) stream_range<FMT, R16, U16, 8, 1, T>(tb.m, tb.cost, nmat, lo, hi, token, lane, hint);
 }
 
 static int cu_count() {
@@ -406,8 +367,8 @@ static int cu_count() {
    streams).  q4: spans of about 48 KiB per wave, 8 rows x 1 block per lane per step (eight rows
    share each block's activation decode), two register sets in flight; the grid is sized so that
    blocks retire and are replaced throughout the token (21,500 blocks for 4.2 GB).  int8: spans of
-   about SWEEP_SPAN_I8[T] bytes per wave with 8 rows x 1 chunk per lane per step and, for one
-   column, three register sets in flight; tiles with one block per CU reach about half the rate
+   about SWEEP_SPAN_I8 bytes per wave with 8 rows x 1 chunk per lane per step and three register
+   sets in flight; tiles with one block per CU reach about half the rate
    (one wave per SIMD cannot cover the latency at each row group's start). */
 constexpr int SWEEP_BLOCKS_PER_CU_16 = 1;
 constexpr int64_t SWEEP_SPAN_Q4 = 48 << 10;
@@ -419,7 +380,7 @@ constexpr int64_t SWEEP_SPAN_Q4 = 48 << 10;
 constexpr int64_t SWEEP_SPAN_16 = 48 << 10;
 constexpr int64_t SWEEP16_TILES_FROM = int64_t{8} << 30;
 constexpr int SPAN16_R = 2, SPAN16_U = 8;
-constexpr int64_t SWEEP_SPAN_I8[4] = {32 << 10, 32 << 10, 128 << 10, 128 << 10};   /* T = 1, 2, 4, 8 */
+constexpr int64_t SWEEP_SPAN_I8 = 32 << 10;
 
 /* Grid of a span-scheduled sweep: about `target` bytes per wave, at least one wave per SIMD; *span
    receives the bytes per wave, ceil(total / waves). */
@@ -443,101 +404,74 @@ static void fill_table_arg(TableArg<N>& tb, const DevMat* htab, int nmat) {
 
 /* One span-scheduled launch: the table by value when the host table is given (nmat <= TABLE_ARG_MAX),
    else from the device table. */
-template <int FMT, int T>
-static void launch_sweep_spans(dim3 g, int64_t span, hipStream_t s, const DevMat* tab, const int64_t* cost,
-                               const DevMat* htab, int nmat, int64_t total, int32_t token) {
+template <int FMT, int T = 1>
+static hipError_t launch_sweep_spans(int64_t target, hipStream_t s, const DevMat* tab, const int64_t* cost,
+                                     const DevMat* htab, int nmat, int64_t total, int32_t token) {
     constexpr int R = (FMT == FMT_F16 || FMT == FMT_BF16) ? SPAN16_R : 4;
     constexpr int U = (FMT == FMT_F16 || FMT == FMT_BF16) ? SPAN16_U : 4;
+    dim3 g;
+    int64_t span = 0;
+    const hipError_t e = span_grid(total, target, g, &span);
+    if (e != hipSuccess) return e;
     if (htab && nmat <= TABLE_ARG_SMALL) {
         TableArg<TABLE_ARG_SMALL> tb;
         fill_table_arg(tb, htab, nmat);
-        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, T, TABLE_ARG_SMALL>), g, dim3(BLOCK), 0, s, tb, nmat, total, span,
-                           token);
+        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, TABLE_ARG_SMALL, T>), g, dim3(BLOCK), 0, s, tb, nmat, total, span, token);
     } else if (htab) {
         TableArg<TABLE_ARG_MAX> tb;
         fill_table_arg(tb, htab, nmat);
-        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, T, TABLE_ARG_MAX>), g, dim3(BLOCK), 0, s, tb, nmat, total, span,
-                           token);
+        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, TABLE_ARG_MAX, T>), g, dim3(BLOCK), 0, s, tb, nmat, total, span, token);
     } else {
-        hipLaunchKernelGGL((k_sweep<FMT, SCHED_SPANS, R, U, 8, 1, 2, T>), g, dim3(BLOCK), 0, s, tab, cost, nmat,
-                           total, span, (int64_t)0, token, nullptr);
-    }
-}
-
-/* q4 and int8 sweeps (T <= 8) over spans. */
-template <int FMT>
-static hipError_t launch_sweep_quant(int T, hipStream_t s, const DevMat* tab, const int64_t* cost, const DevMat* htab,
-                                     int nmat, int64_t total, int32_t token) {
-    const int ti = T == 1 ? 0 : T == 2 ? 1 : T == 4 ? 2 : 3;
-    dim3 g;
-    int64_t span = 0;
-    const hipError_t e = span_grid(total, FMT == FMT_Q4 ? SWEEP_SPAN_Q4 : SWEEP_SPAN_I8[ti], g, &span);
-    if (e != hipSuccess) return e;
-    switch (T) {
-        case 1: launch_sweep_spans<FMT, 1>(g, span, s, tab, cost, htab, nmat, total, token); break;
-        case 2: launch_sweep_spans<FMT, 2>(g, span, s, tab, cost, htab, nmat, total, token); break;
-        case 4: launch_sweep_spans<FMT, 4>(g, span, s, tab, cost, htab, nmat, total, token); break;
-        case 8: launch_sweep_spans<FMT, 8>(g, span, s, tab, cost, htab, nmat, total, token); break;
-        default: return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_sweep<FMT, SCHED_SPANS, R, U, 8, 1, T>), g, dim3(BLOCK), 0, s, tab, cost, nmat, total, span,
+                           (int64_t)0, token, nullptr);
     }
     return hipGetLastError();
 }
 
-/* Which launches run over spans (those may take their table by value). */
-static bool sweep_spans(int64_t total, int fmt_all, int T) {
+/* Which single-token launches run over spans (those may take their table by value). */
+static bool sweep_spans(int64_t total, int fmt_all) {
     return fmt_all == FMT_Q4 || fmt_all == FMT_I8 ||
-           ((fmt_all == FMT_F16 || fmt_all == FMT_BF16) && T == 1 && total < SWEEP16_TILES_FROM);
+           ((fmt_all == FMT_F16 || fmt_all == FMT_BF16) && total < SWEEP16_TILES_FROM);
 }
 
-bool sweep_table_by_value(int nmat, int64_t total, int fmt_all, int T) {
-    return nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all, T);
+/* int8 with two columns in long streams: two packed dot products per code pair are no burden to the
+   vector ALUs, and the two-column form of the sweep's loop streams best (per pass against the
+   matrix-core form, which forms four columns whatever it is asked for: the 72B model 0.732 and 0.742
+   ms, a 0.6 GB model of 2,048-wide layers 95 and 109 us). */
+static bool sweep_i8_pair(const DevMat* htab, int nmat, int fmt_all, int T) {
+    return T == 2 && fmt_all == FMT_I8 && !cols_takes_split(htab, nmat, fmt_all, T);
 }
 
-/* 16-bit (or mixed-format) sweep over tiles, tokens token .. token + T - 1 per weight pass. */
-template <int FMT, int T>
-static void launch_sweep_tiles(dim3 grid, hipStream_t s, const DevMat* tab, const int64_t* cost, int nmat,
-                               int64_t total, int64_t tile, int32_t token, unsigned* ctr) {
-    hipLaunchKernelGGL((k_sweep<FMT, SCHED_TILES, 4, 4, 8, 1, 2, T>), grid, dim3(BLOCK), 0, s, tab, cost, nmat,
-                       total, (int64_t)0, tile, token, ctr);
-}
-
-template <int FMT>
-static hipError_t launch_sweep_cols(dim3 grid, int T, hipStream_t s, const DevMat* tab, const int64_t* cost,
-                                    int nmat, int64_t total, int64_t tile, int32_t token, unsigned* ctr) {
-    switch (T) {
-        case 1: launch_sweep_tiles<FMT, 1>(grid, s, tab, cost, nmat, total, tile, token, ctr); break;
-        case 2: launch_sweep_tiles<FMT, 2>(grid, s, tab, cost, nmat, total, tile, token, ctr); break;
-        case 4: launch_sweep_tiles<FMT, 4>(grid, s, tab, cost, nmat, total, tile, token, ctr); break;
-        case 8: launch_sweep_tiles<FMT, 8>(grid, s, tab, cost, nmat, total, tile, token, ctr); break;
-        case 16: launch_sweep_tiles<FMT, 16>(grid, s, tab, cost, nmat, total, tile, token, ctr); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+bool sweep_table_by_value(const DevMat* htab, int nmat, int64_t total, int fmt_all, int T) {
+    if (T > 1 && !sweep_i8_pair(htab, nmat, fmt_all, T)) return nmat <= COLS_TABLE_ARG;
+    return nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all);
 }
 
 hipError_t launch_sweep(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total,
                         int fmt_all, int32_t token, int T, unsigned* ctr, hipStream_t s) {
     if (nmat == 0 || total == 0) return hipSuccess;
-    if (!sweep_table_by_value(nmat, total, fmt_all, T)) htab = nullptr;
-    if (fmt_all == FMT_Q4) return launch_sweep_quant<FMT_Q4>(T, s, tab, cost, htab, nmat, total, token);
-    if (fmt_all == FMT_I8) return launch_sweep_quant<FMT_I8>(T, s, tab, cost, htab, nmat, total, token);
-    if (sweep_spans(total, fmt_all, T)) {
-        dim3 g;
-        int64_t span = 0;
-        const hipError_t e = span_grid(total, SWEEP_SPAN_16, g, &span);
-        if (e != hipSuccess) return e;
-        if (fmt_all == FMT_F16) launch_sweep_spans<FMT_F16, 1>(g, span, s, tab, cost, htab, nmat, total, token);
-        else launch_sweep_spans<FMT_BF16, 1>(g, span, s, tab, cost, htab, nmat, total, token);
-        return hipGetLastError();
-    }
+    const bool pair = sweep_i8_pair(htab, nmat, fmt_all, T);
+    if (T > 1 && !pair) return launch_cols(tab, cost, htab, nmat, total, fmt_all, token, T, s);
+    if (!sweep_table_by_value(htab, nmat, total, fmt_all, T)) htab = nullptr;
+    if (pair) return launch_sweep_spans<FMT_I8, 2>(SWEEP_SPAN_I8, s, tab, cost, htab, nmat, total, token);
+    if (fmt_all == FMT_Q4) return launch_sweep_spans<FMT_Q4>(SWEEP_SPAN_Q4, s, tab, cost, htab, nmat, total, token);
+    if (fmt_all == FMT_I8) return launch_sweep_spans<FMT_I8>(SWEEP_SPAN_I8, s, tab, cost, htab, nmat, total, token);
+    if (sweep_spans(total, fmt_all))
+        return fmt_all == FMT_F16 ? launch_sweep_spans<FMT_F16>(SWEEP_SPAN_16, s, tab, cost, htab, nmat, total, token)
+                                  : launch_sweep_spans<FMT_BF16>(SWEEP_SPAN_16, s, tab, cost, htab, nmat, total, token);
+    /* 16-bit (or mixed-format) sweep over tiles */
     const dim3 grid((unsigned)(cu_count() * SWEEP_BLOCKS_PER_CU_16));
     const int64_t tile = sweep_tile(total, (int64_t)grid.x * WAVES_PER_BLOCK);
+#define WSR_TILES(F)                                                                                               \
+    hipLaunchKernelGGL((k_sweep<F, SCHED_TILES, 4, 4, 8, 1>), grid, dim3(BLOCK), 0, s, tab, cost, nmat, total, \
+                       (int64_t)0, tile, token, ctr)
     switch (fmt_all) {
-        case FMT_F16: return launch_sweep_cols<FMT_F16>(grid, T, s, tab, cost, nmat, total, tile, token, ctr);
-        case FMT_BF16: return launch_sweep_cols<FMT_BF16>(grid, T, s, tab, cost, nmat, total, tile, token, ctr);
-        default:   /* mixed formats; a table holding q4 or int8 comes with T <= 8 */
-            return launch_sweep_cols<0>(grid, T, s, tab, cost, nmat, total, tile, token, ctr);
+        case FMT_F16: WSR_TILES(FMT_F16); break;
+        case FMT_BF16: WSR_TILES(FMT_BF16); break;
+        default: WSR_TILES(0); break;
     }
+#undef WSR_TILES
+    return hipGetLastError();
 }
 
 /* ================================ allocation-free sweep scratch ================================ */
