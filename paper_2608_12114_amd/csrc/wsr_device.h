@@ -649,10 +649,12 @@ struct I8Step {
 
 /* Rows [r0, r1) of an int8 matrix, one column, with NB register sets in flight: while one unit
    (group of R rows, step) is decoded the loads of the next NB - 1 units are outstanding, across
-   row-group boundaries, as in the q4 loop below.  Needs rows made of whole steps (nc a multiple of
-   64 U); otherwise, and for the rows left over, group_i8 runs.  Every sum takes the chunks and
-   the reduction tree of group_i8, so the results are those of rows_i8. */
-template <int R, int U, int NB>
+   row-group boundaries, as in the q4 loop below.  Rows that are no whole number of steps (RAGGED) end
+   in a step whose lanes past the row's end load its last chunk again and multiply it by zero
+   activations, which adds nothing (codes are finite).  The rows left over go through group_i8.
+   Every sum takes the chunks and the reduction tree of group_i8, so the results are those of
+   rows_i8. */
+template <int R, int U, int NB, bool RAGGED>
 __device__ __forceinline__ void rows_i8_pipe(const DevMat& d, int64_t r0, int64_t r1, int32_t token, int lane) {
     g_u32x4* Wq = as_global<g_u32x4*>(d.w);
     const uint16_t* S = static_cast<const uint16_t*>(d.s);
@@ -662,8 +664,8 @@ __device__ __forceinline__ void rows_i8_pipe(const DevMat& d, int64_t r0, int64_
     constexpr int STEP = WAVE * U;
     const int64_t ngroups = (r1 - r0) / R;
     int64_t i = r0;
-    if (ngroups > 0 && nc > 0 && nc % STEP == 0) {
-        const int64_t steps = nc / STEP;                 /* steps per row group */
+    if (ngroups > 0 && nc > 0) {
+        const int64_t steps = RAGGED ? (nc + STEP - 1) / STEP : nc / STEP;   /* steps per row group */
         const int64_t n = ngroups * steps;               /* units */
         float acc[R];
 #pragma unroll
@@ -674,7 +676,8 @@ __device__ __forceinline__ void rows_i8_pipe(const DevMat& d, int64_t r0, int64_
             const int64_t i0 = r0 + gl * R;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t c = kl * STEP + u * WAVE + lane;
+                int64_t c = kl * STEP + u * WAVE + lane;
+                if constexpr (RAGGED) c = std::min<int64_t>(c, nc - 1);
                 st.x[u][0] = load_reused(x + 2 * c);
                 st.x[u][1] = load_reused(x + 2 * c + 1);
 #pragma unroll
@@ -682,7 +685,11 @@ __device__ __forceinline__ void rows_i8_pipe(const DevMat& d, int64_t r0, int64_
             }
             if (++kl == steps) { kl = 0; ++gl; }
         };
-        auto decode = [&](const I8Step<R, U>& st) {
+        auto decode = [&](I8Step<R, U>& st) {
+            if (RAGGED && kc + 1 == steps)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (kc * STEP + u * WAVE + lane >= nc) st.x[u][0] = st.x[u][1] = zero4();
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 I8X q;
@@ -728,13 +735,16 @@ __device__ __forceinline__ void rows_i8_pipe(const DevMat& d, int64_t r0, int64_
     for (; i < r1; ++i) group_i8<1, U, 1>(Wq, S, x, 0, y, 0, nc, i, lane);
 }
 
-/* Rows [r0, r1) of a q4 matrix.  With NB >= 2, when rows hold whole steps (nb a multiple of 64 U),
-   the units (group of R rows, step) run as one software pipeline over NB register sets: the loads
-   of the NB - 1 units after the current one are in flight while it is decoded.  The main loop is
-   unrolled by NB so every set is named statically and its loads are unconditional, which keeps
-   the waits exact; the last units are decoded after it.  Remaining rows go one at a time. */
-template <int R, int U, int NB = 2>
-__device__ __forceinline__ void rows_q4(const DevMat& d, int64_t r0, int64_t r1, int32_t token,
+/* Rows [r0, r1) of a q4 matrix: the units (group of R rows, step) run as one software pipeline over NB
+   register sets: the loads of the NB - 1 units after the current one are in flight while it is
+   decoded.  The main loop is unrolled by NB so every set is named statically and its loads are
+   unconditional, which keeps the waits exact; the last units are decoded after it.  Rows that are no
+   whole number of steps (RAGGED: nb no multiple of 64 U) end in a step whose lanes past the row's
+   end load its last block again, to be multiplied by zero activations and a zero scale, which adds
+   nothing (codes are finite); one row at a time, as such rows went before, a row's latency was the
+   rate (eight layers of 1,024 wide: 0.45 TB/s).  Remaining rows go one at a time. */
+template <int R, int U, int NB, bool RAGGED>
+__device__ __forceinline__ void rows_q4_pipe(const DevMat& d, int64_t r0, int64_t r1, int32_t token,
                                         int lane) {
     g_u32x4* Wq = as_global<g_u32x4*>(d.w);
     g_u16* S = as_global<g_u16*>(d.s);
@@ -744,10 +754,8 @@ __device__ __forceinline__ void rows_q4(const DevMat& d, int64_t r0, int64_t r1,
     constexpr int STEP = WAVE * U;
     const int64_t ngroups = (r1 - r0) / R;
     int64_t i_end = r0 + ngroups * R;
-    if (NB < 2) {
-        for (int64_t i = r0; i < i_end; i += R) q4_group<R, U>(Wq, S, x, y, nb, i, lane);
-    } else if (ngroups > 0 && nb % STEP == 0 && nb > 0) {
-        const int64_t steps = nb / STEP;                 /* steps per row group */
+    if (ngroups > 0 && nb > 0) {
+        const int64_t steps = RAGGED ? (nb + STEP - 1) / STEP : nb / STEP;   /* steps per row group */
         const int64_t n = ngroups * steps;               /* units */
         float acc[R];
 #pragma unroll
@@ -769,21 +777,44 @@ __device__ __forceinline__ void rows_q4(const DevMat& d, int64_t r0, int64_t r1,
                 rsc = buffer_of(uniform_ptr(static_cast<const char*>(d.s) + i * nb * 2));
             }
             const uint32_t kb = (uint32_t)(kl * STEP);   /* the step's first block */
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    st.x[u][j] = buf_reused(rx, vx + (uint32_t)(4096 * u + 16 * j), 64u * kb);
-#pragma unroll
-            for (int r = 0; r < R; ++r)
+            if constexpr (RAGGED) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    st.w[r][u] = buf_once(rw, vl + (uint32_t)(1024 * u), r * rcb + 16u * kb);
-                    st.s[r][u] = (uint16_t)buf_u16(rsc, (vl >> 3) + (uint32_t)(128 * u), r * rsb + 2u * kb);
+                    const uint32_t c = std::min(kb + (uint32_t)(u * WAVE + lane), (uint32_t)nb - 1);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) st.x[u][j] = buf_reused(rx, 64u * c + (uint32_t)(16 * j), 0);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        st.w[r][u] = buf_once(rw, 16u * c, r * rcb);
+                        st.s[r][u] = (uint16_t)buf_u16(rsc, 2u * c, r * rsb);
+                    }
                 }
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        st.x[u][j] = buf_reused(rx, vx + (uint32_t)(4096 * u + 16 * j), 64u * kb);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        st.w[r][u] = buf_once(rw, vl + (uint32_t)(1024 * u), r * rcb + 16u * kb);
+                        st.s[r][u] = (uint16_t)buf_u16(rsc, (vl >> 3) + (uint32_t)(128 * u), r * rsb + 2u * kb);
+                    }
+            }
             if (++kl == steps) { kl = 0; ++gl; }
         };
-        auto decode = [&](const Q4Step<R, U>& st) {
+        auto decode = [&](Q4Step<R, U>& st) {
+            if (RAGGED && kc + 1 == steps)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (kc * STEP + u * WAVE + lane >= nb) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) st.x[u][j] = zero4();
+#pragma unroll
+                        for (int r = 0; r < R; ++r) st.s[r][u] = 0;
+                    }
             q4_compute<R, U>(st, acc);
             if (kc + 1 == steps) q4_store<R>(y, r0 + gc * R, acc, lane);
             if (++kc == steps) { kc = 0; ++gc; }
@@ -813,6 +844,21 @@ __device__ __forceinline__ void rows_q4(const DevMat& d, int64_t r0, int64_t r1,
     }
     for (int64_t i = i_end; i < r1; ++i) q4_group<1, U>(Wq, S, x, y, nb, i, lane);
 }
+
+template <int R, int U, int NB = 2>
+__device__ __forceinline__ void rows_q4(const DevMat& d, int64_t r0, int64_t r1, int32_t token, int lane) {
+    if (d.nc >= (1 << 24)) {                             /* a group's 32-bit offsets would not reach */
+        g_u32x4* x = as_global<g_u32x4*>(static_cast<const char*>(d.x) + token * d.x_stride);
+        g_f32* y = as_global<g_f32*>(reinterpret_cast<char*>(d.y) + token * d.y_stride);
+        for (int64_t i = r0; i < r1; ++i)
+            q4_group<1, 1>(as_global<g_u32x4*>(d.w), as_global<g_u16*>(d.s), x, y, d.nc, i, lane);
+    } else if (d.nc % (WAVE * U) == 0) {
+        rows_q4_pipe<R, U, NB, false>(d, r0, r1, token, lane);
+    } else {
+        rows_q4_pipe<R, U, NB, true>(d, r0, r1, token, lane);
+    }
+}
+
 
 /* ceil(a / b) for a >= 0, b > 0.  A 64-bit division expands to a long dependent sequence on this
    target, so values that fit 32 bits (every range of a matrix below 4 GiB) take the 32-bit form. */
@@ -862,8 +908,9 @@ __device__ __forceinline__ void stream_range(const DevMat* __restrict__ tab, con
         else if ((FMT == 0 || FMT == FMT_Q4) && fmt == FMT_Q4)
             rows_q4<RQ, UQ>(d, r0, r1, token, lane);
         else if ((FMT == 0 || FMT == FMT_I8) && fmt == FMT_I8) {
-            if constexpr (T == 1) rows_i8_pipe<I8_R, 1, I8_NB>(d, r0, r1, token, lane);
-            else rows_i8<I8_R, T>(d, r0, r1, token, lane);
+            if constexpr (T != 1) rows_i8<I8_R, T>(d, r0, r1, token, lane);
+            else if (d.nc % WAVE == 0) rows_i8_pipe<I8_R, 1, I8_NB, false>(d, r0, r1, token, lane);
+            else rows_i8_pipe<I8_R, 1, I8_NB, true>(d, r0, r1, token, lane);
         }
     }
 }
