@@ -47,7 +47,7 @@ constexpr int cols_lds_bytes() {
 
 template <int FMT, int TQ, int WAVES, int N>
 __global__ __launch_bounds__(WAVE * WAVES) __attribute__((amdgpu_waves_per_eu(FMT == 0 ? 2 : WAVES / 2)))
-void k_cols(ColsTable<N> tb, int nmat, int64_t total, int64_t span, int32_t token, int ntok) {
+void k_cols(int nmat, int32_t token, int64_t total, int64_t span, int ntok, ColsTable<N> tb) {
     __shared__ __align__(16) char lds[cols_lds_bytes<FMT, TQ>()];
     const int64_t lo = (int64_t)blockIdx.x * span, hi = std::min<int64_t>(total, lo + span);
     if (lo < hi)
@@ -57,7 +57,7 @@ void k_cols(ColsTable<N> tb, int nmat, int64_t total, int64_t span, int32_t toke
 
 template <int FMT, int TQ, int RG, int N>
 __global__ __launch_bounds__(4 * WAVE) __attribute__((amdgpu_waves_per_eu(2)))
-void k_split(ColsTable<N> tb, int nmat, int64_t total, int64_t span, int32_t token, int ntok) {
+void k_split(int nmat, int32_t token, int64_t total, int64_t span, int ntok, ColsTable<N> tb) {
     __shared__ __align__(16) char lds[split_lds_bytes<FMT, TQ, RG>()];
     const int64_t lo = (int64_t)blockIdx.x * span, hi = std::min<int64_t>(total, lo + span);
     if (lo < hi)
@@ -119,7 +119,7 @@ static hipError_t launch_split(const ColsTable<N>& tb, const DevMat* htab, int n
     const hipError_t e = cols_grid(htab, nmat, total, 4 * RG, std::max<int64_t>(SPLIT_BLOCKS, (total + bytes - 1) / bytes), g,
                                    &span);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_split<FMT, TQ, RG, N>), g, dim3(4 * WAVE), 0, s, tb, nmat, total, span, token, T);
+    hipLaunchKernelGGL((k_split<FMT, TQ, RG, N>), g, dim3(4 * WAVE), 0, s, nmat, token, total, span, T, tb);
     return hipGetLastError();
 }
 
@@ -146,7 +146,7 @@ static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int n
         const hipError_t e = cols_grid(htab, nmat, total, COLS_ROUND,
                                        COLS_BLOCKS * std::max<int64_t>(1, (total + bytes / 2) / bytes), g, &span);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_cols<FMT, TQ, WAVES, N>), g, dim3(WAVE * WAVES), 0, s, tb, nmat, total, span, token, T);
+        hipLaunchKernelGGL((k_cols<FMT, TQ, WAVES, N>), g, dim3(WAVE * WAVES), 0, s, nmat, token, total, span, T, tb);
         return hipGetLastError();
     }
     return hipErrorInvalidValue;

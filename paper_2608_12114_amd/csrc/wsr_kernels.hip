@@ -118,9 +118,26 @@ hipError_t launch_probe(const float* buf, int64_t n, double* sum_dev, void* ws, 
 
 /* ======================================= GEMVs ================================================ */
 
+/* A GEMV's matrix travels as single arguments, which the command processor puts into registers before
+   the first instruction (the build asks for 16 of them; a structure by value stays in memory): the
+   loads of the weights then wait for nothing. */
+#define WSR_GEMV_ARGS const void *w, const void *sc, const void *x, float *y, int64_t M, int64_t nc
+__device__ __forceinline__ DevMat gemv_mat(WSR_GEMV_ARGS) {
+    DevMat d{};
+    d.w = w;
+    d.s = sc;
+    d.x = x;
+    d.y = y;
+    d.M = M;
+    d.nc = nc;
+    return d;
+}
+#define WSR_GEMV_MAT const DevMat d = gemv_mat(w, sc, x, y, M, nc)
+
 /* One wave per R consecutive rows. */
 template <int FMT, int R, int U>
-__global__ __launch_bounds__(BLOCK) void k_gemv16(DevMat d) {
+__global__ __launch_bounds__(BLOCK) void k_gemv16(WSR_GEMV_ARGS) {
+    WSR_GEMV_MAT;
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
     const int64_t r0 = wave * R;
@@ -129,7 +146,8 @@ __global__ __launch_bounds__(BLOCK) void k_gemv16(DevMat d) {
 }
 
 template <int R, int U>
-__global__ __launch_bounds__(BLOCK) void k_gemv_q4(DevMat d) {
+__global__ __launch_bounds__(BLOCK) void k_gemv_q4(WSR_GEMV_ARGS) {
+    WSR_GEMV_MAT;
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
     const int64_t r0 = wave * R;
@@ -141,14 +159,15 @@ template <typename K>
 static hipError_t launch_rows(K kernel, const DevMat& m, int R, hipStream_t s) {
     const int64_t waves = (m.M + R - 1) / R;
     const int64_t blocks = (waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(BLOCK), 0, s, m);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(BLOCK), 0, s, m.w, m.s, m.x, m.y, m.M, m.nc);
     return hipGetLastError();
 }
 
 /* One group of R rows per wave.  The full and the partial group take separate branches rather than
    a clamp of the row end: the clamp's select was miscompiled (the pre-emit peephole dropped the
    instruction that set the select's condition, so the end became r0 + R past the last row). */
-__global__ __launch_bounds__(BLOCK) void k_gemv_i8(DevMat d) {
+__global__ __launch_bounds__(BLOCK) void k_gemv_i8(WSR_GEMV_ARGS) {
+    WSR_GEMV_MAT;
     constexpr int R = I8_GEMV_R;
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
@@ -168,6 +187,15 @@ __global__ __launch_bounds__(BLOCK) void k_gemv16_pair(DevMat d) {
     rows16_cols<FMT, PAIR16_R, 4, 2>(d, r0, std::min<int64_t>(r0 + PAIR16_R, d.M), 0, lane);
 }
 
+static hipError_t launch_gemv16_pair(const DevMat& m, hipStream_t s) {
+    const int64_t rows = WAVES_PER_BLOCK * PAIR16_R, blocks = (m.M + rows - 1) / rows;
+    if (m.fmt == FMT_F16)
+        hipLaunchKernelGGL(k_gemv16_pair<FMT_F16>, dim3((unsigned)blocks), dim3(BLOCK), 0, s, m);
+    else
+        hipLaunchKernelGGL(k_gemv16_pair<FMT_BF16>, dim3((unsigned)blocks), dim3(BLOCK), 0, s, m);
+    return hipGetLastError();
+}
+
 /* Where a matrix has rows for four waves per SIMD, two columns cost the vector ALUs little and whole
    rows per wave, with no sums to join, win over the matrix-core form (us, this and that: 20,000 x
    1,024 f16 8.1 and 10.5, 20,000 x 4,096 27.4 and 29.2, 100,000 x 4,096 bf16 121 and 128; 8,192 x
@@ -178,8 +206,7 @@ static bool gemv16_pair(const DevMat& m, int T) {
 
 hipError_t launch_gemv_cols(const DevMat& m, int T, hipStream_t s) {
     if (gemv16_pair(m, T))
-        return m.fmt == FMT_F16 ? launch_rows(k_gemv16_pair<FMT_F16>, m, PAIR16_R, s)
-                                : launch_rows(k_gemv16_pair<FMT_BF16>, m, PAIR16_R, s);
+        return launch_gemv16_pair(m, s);
     if (T > 1 && m.nc <= COLS_MAX_NC) return launch_cols(nullptr, nullptr, &m, 1, m.M * m.row_bytes, m.fmt, 0, T, s);
     DevMat d = m;                                   /* one column, or rows too long: column by column */
     for (int t = 0; t < T; ++t) {
@@ -341,13 +368,61 @@ struct TableArg {
 static_assert(sizeof(TableArg<TABLE_ARG_MAX>) + 32 <= 32000, "the by-value table must stay within the checked argument size");
 
 template <int FMT, int R16, int U16, int N, int T>
-__global__ __launch_bounds__(BLOCK) void k_sweep_arg(TableArg<N> tb, int nmat, int64_t total, int64_t span,
-                                                     int32_t token) {
+__global__ __launch_bounds__(BLOCK) void k_sweep_arg(int nmat, int32_t token, int64_t total, int64_t span,
+                                                     TableArg<N> tb) {
     const int lane = threadIdx.x & (WAVE - 1);
     int hint = 0;
     int64_t lo, hi;
     span_bounds(total, span_wave(), span, lo, hi);
     if (lo < hi) stream_range<FMT, R16, U16, 8, 1, T>(tb.m, tb.cost, nmat, lo, hi, token, lane, hint);
+}
+
+/* Short streams: up to SHORT_MATS matrices, one group of rows per wave, blocks given to the matrices in
+   turn by the host (f1 .. f7: the first block of matrices 1 .. 7, in registers when the kernel starts;
+   one read of the argument memory then brings the matrix).  Such a launch lasts a few us, most of it
+   before the first load and after the last: the sweep's spans spend that on looking up their rows
+   (bisection, division) and give each wave eight rows or more, this form starts at once and has
+   more waves (a launch of the 8B model's q, k and v in q4: 6.4 -> 4.4 us). */
+constexpr int SHORT_MATS = 8;
+struct ShortTable {
+    DevMat m[SHORT_MATS];
+};
+
+template <int FMT, int R, int U>
+__global__ __launch_bounds__(BLOCK) void k_sweep_short(int f1, int f2, int f3, int f4, int f5, int f6, int f7,
+                                                       int32_t token, ShortTable tb) {
+    const int lane = threadIdx.x & (WAVE - 1), b = (int)blockIdx.x;
+    const int m = (b >= f1) + (b >= f2) + (b >= f3) + (b >= f4) + (b >= f5) + (b >= f6) + (b >= f7);
+    const int first = m == 0 ? 0 : m == 1 ? f1 : m == 2 ? f2 : m == 3 ? f3 : m == 4 ? f4 : m == 5 ? f5 : m == 6 ? f6 : f7;
+    const DevMat& d = tb.m[m];
+    const int64_t r0 = ((int64_t)(b - first) * WAVES_PER_BLOCK + wave_in_block()) * R;
+    if (r0 >= d.M) return;
+    if (d.M - r0 >= R) {
+        if constexpr (FMT == FMT_Q4) rows_q4<R, U, 2>(d, r0, r0 + R, token, lane);
+        else if constexpr (FMT == FMT_I8) rows_i8<R>(d, r0, r0 + R, token, lane);
+        else rows16<FMT, R, U>(d, r0, r0 + R, token, lane);
+    } else {
+        if constexpr (FMT == FMT_Q4) rows_q4<1, U, 2>(d, r0, d.M, token, lane);
+        else if constexpr (FMT == FMT_I8) rows_i8<1>(d, r0, d.M, token, lane);
+        else rows16<FMT, 1, U>(d, r0, d.M, token, lane);
+    }
+}
+
+template <int FMT, int R, int U>
+static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipStream_t s) {
+    ShortTable tb;
+    int f[SHORT_MATS + 1];
+    int64_t blocks = 0;
+    for (int i = 0; i < SHORT_MATS; ++i) {
+        f[i] = i < nmat ? (int)blocks : INT32_MAX;
+        if (i >= nmat) continue;
+        tb.m[i] = htab[i];
+        blocks += (htab[i].M + WAVES_PER_BLOCK * R - 1) / (WAVES_PER_BLOCK * R);
+        if (blocks >= INT32_MAX) return hipErrorInvalidValue;
+    }
+    hipLaunchKernelGGL((k_sweep_short<FMT, R, U>), dim3((unsigned)blocks), dim3(BLOCK), 0, s, f[1], f[2], f[3], f[4], f[5],
+                       f[6], f[7], token, tb);
+    return hipGetLastError();
 }
 
 static int cu_count() {
@@ -416,11 +491,11 @@ static hipError_t launch_sweep_spans(int64_t target, hipStream_t s, const DevMat
     if (htab && nmat <= TABLE_ARG_SMALL) {
         TableArg<TABLE_ARG_SMALL> tb;
         fill_table_arg(tb, htab, nmat);
-        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, TABLE_ARG_SMALL, T>), g, dim3(BLOCK), 0, s, tb, nmat, total, span, token);
+        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, TABLE_ARG_SMALL, T>), g, dim3(BLOCK), 0, s, nmat, token, total, span, tb);
     } else if (htab) {
         TableArg<TABLE_ARG_MAX> tb;
         fill_table_arg(tb, htab, nmat);
-        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, TABLE_ARG_MAX, T>), g, dim3(BLOCK), 0, s, tb, nmat, total, span, token);
+        hipLaunchKernelGGL((k_sweep_arg<FMT, R, U, TABLE_ARG_MAX, T>), g, dim3(BLOCK), 0, s, nmat, token, total, span, tb);
     } else {
         hipLaunchKernelGGL((k_sweep<FMT, SCHED_SPANS, R, U, 8, 1, T>), g, dim3(BLOCK), 0, s, tab, cost, nmat, total, span,
                            (int64_t)0, token, nullptr);
@@ -434,6 +509,15 @@ static bool sweep_spans(int64_t total, int fmt_all) {
            ((fmt_all == FMT_F16 || fmt_all == FMT_BF16) && total < SWEEP16_TILES_FROM);
 }
 
+/* Single-token launches of one format over few matrices and at most SHORT_BYTES take k_sweep_short.
+   Measured as chains of launches, short form against spans (us): the 8B model's layer (14 to 66 MB a
+   launch) q4 1,139 and 1,395 for 32 layers and the head, int8 46.5 and 52.3 for one layer, bf16 71.7
+   and 77.4; the layer as one launch (122 to 436 MB) q4 24.5 and 24.7, int8 37.2 and 38.4, bf16 equal. */
+constexpr int64_t SHORT_BYTES = 256 << 20;
+static bool sweep_short(int nmat, int64_t total, int fmt_all) {
+    return nmat <= SHORT_MATS && total <= SHORT_BYTES && fmt_all != 0;
+}
+
 /* int8 with two columns in long streams: two packed dot products per code pair are no burden to the
    vector ALUs, and the two-column form of the sweep's loop streams best (per pass against the
    matrix-core form, which forms four columns whatever it is asked for: the 72B model 0.732 and 0.742
@@ -444,12 +528,20 @@ static bool sweep_i8_pair(const DevMat* htab, int nmat, int fmt_all, int T) {
 
 bool sweep_table_by_value(const DevMat* htab, int nmat, int64_t total, int fmt_all, int T) {
     if (T > 1 && !sweep_i8_pair(htab, nmat, fmt_all, T)) return nmat <= COLS_TABLE_ARG;
-    return nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all);
+    return (T == 1 && sweep_short(nmat, total, fmt_all)) || (nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all));
 }
 
 hipError_t launch_sweep(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total,
                         int fmt_all, int32_t token, int T, unsigned* ctr, hipStream_t s) {
     if (nmat == 0 || total == 0) return hipSuccess;
+    if (T == 1 && sweep_short(nmat, total, fmt_all)) {
+        switch (fmt_all) {
+            case FMT_Q4: return launch_short<FMT_Q4, 4, 1>(htab, nmat, token, s);
+            case FMT_I8: return launch_short<FMT_I8, 2, 1>(htab, nmat, token, s);
+            case FMT_F16: return launch_short<FMT_F16, 1, 4>(htab, nmat, token, s);
+            default: return launch_short<FMT_BF16, 1, 4>(htab, nmat, token, s);
+        }
+    }
     const bool pair = sweep_i8_pair(htab, nmat, fmt_all, T);
     if (T > 1 && !pair) return launch_cols(tab, cost, htab, nmat, total, fmt_all, token, T, s);
     if (!sweep_table_by_value(htab, nmat, total, fmt_all, T)) htab = nullptr;
