@@ -125,14 +125,6 @@ __device__ __forceinline__ uint32_t col_pair(const u32x4& w, int k) {
     }
 }
 
-/* Orders the workgroup's LDS accesses on both sides of it and nothing else: loads from memory stay in
-   flight across it (__syncthreads would wait for them). */
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 /* Totals over the 16 lane groups of E per-lane entries (lane 4 b + j: row j, partial sums of group
    b), with levels 2 to 5 of the tree of wave_sum_entries: b ^ 15, b ^ 7, b ^ 2, b ^ 1.  Every level's
    sums are the same for all groups the earlier levels joined, so b ^ 8 serves for b ^ 7 and b ^ 4

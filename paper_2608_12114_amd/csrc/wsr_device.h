@@ -84,6 +84,14 @@ __device__ __forceinline__ int wave_in_block() {
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
 }
 
+/* Orders the workgroup's LDS accesses on both sides of it and nothing else: loads from memory stay in
+   flight across it (__syncthreads would wait for them). */
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 /* acc + a.lo*b.lo + a.hi*b.hi for two packed 16-bit pairs, fp32 accumulate. */
 template <int FMT>
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {

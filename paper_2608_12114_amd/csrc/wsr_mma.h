@@ -199,10 +199,14 @@ __device__ __forceinline__ void wait_vm() {
    steps (below); otherwise each is loaded into registers alone.
    The caller keeps 16 NT rows of codes and 16 tokens of activations within 2^31 bytes.  The
    activations (and, with WHOLE, the q4 scales) come from the LDS ring, which leaves the register
-   ring to the weights. */
-template <int FMT, int NT, bool WHOLE, bool SHORT>
+   ring to the weights.
+   With KS > 1 the KS waves of a workgroup take the same rows and split their steps: wave p the steps
+   [p steps / KS, (p + 1) steps / KS), and at a group's end they join their sums through LDS (joins:
+   NT KiB per wave), in wave order, each wave storing some of the tiles. */
+template <int FMT, int NT, bool WHOLE, bool SHORT, int KS>
 __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1, int32_t token0, int ntok, int lane,
-                                         u32x4* __restrict__ xlds) {
+                                         int wave, u32x4* __restrict__ xlds, u32x4* __restrict__ joins) {
+    static_assert(KS == 1 || FMT != FMT_Q4, "q4 scales come in blocks of four steps from the first on");
     using Unit = MmaUnit<FMT, NT>;
     constexpr int J = Unit::J, SL = Unit::SL, SK = MmaStep<FMT>::K, SB = 64 * J;   /* SB: row bytes per step */
     constexpr int XG = FMT == FMT_I8 ? 32 : 16;                  /* x bytes per lane group within a step */
@@ -212,15 +216,17 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
     const int64_t kelem = FMT == FMT_Q4 ? nc * 32 : FMT == FMT_I8 ? nc * 16 : nc * 8;
     const int32_t steps = (int32_t)((crb + SB - 1) / SB);       /* at most 2^19 (rows up to 32 MiB) */
     const int64_t ngroups = (r1 - r0 + 16 * NT - 1) / (16 * NT);
-    const int64_t n = ngroups * steps;                           /* units */
-    if (n == 0) return;
+    const int32_t ks = KS == 1 ? 0 : (int32_t)((int64_t)steps * wave / KS);          /* this wave's steps */
+    const int32_t ke = KS == 1 ? steps : (int32_t)((int64_t)steps * (wave + 1) / KS);
+    const int64_t n = ngroups * (ke - ks);                       /* units */
+    if (KS == 1 && n == 0) return;
     const rsrc_t rx = buffer_of(uniform_ptr(static_cast<const char*>(d.x) + (int64_t)token0 * d.x_stride));
     const int64_t srow = FMT == FMT_Q4 ? nc * 2 : 2;             /* scale bytes per row */
     f4_t acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
     int64_t gl = 0, gc = 0;                                      /* group of the next unit to load, multiply */
-    int32_t kl = 0, kc = 0;                                      /* and its step                             */
+    int32_t kl = ks, kc = ks;                                    /* and its step                             */
     int lbuf = 0, mbuf = 0;                                      /* LDS ring half of the next load, multiply */
     rsrc_t rw = buffer_of(d.w), rs = buffer_of(d.w);             /* this group's row r0 of codes, scales */
     uint32_t vr[NT], vs[NT];                                     /* lane offsets: row of each tile */
@@ -266,7 +272,7 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
         }
     };
     auto load = [&](Unit& u) {
-        if (kl == 0) {
+        if (kl == ks) {
             const int64_t i0 = r0 + gl * 16 * NT;
             rw = buffer_of(uniform_ptr(static_cast<const char*>(d.w) + i0 * crb));
             if constexpr (FMT == FMT_Q4 || FMT == FMT_I8)
@@ -323,20 +329,51 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
                     for (int j = 0; j < 4; ++j) u.s[t][j] = h[2 * j] | h[2 * j + 1] << 16;
                 }
             } else if constexpr (FMT == FMT_I8) {
-                if (kl + 1 == steps) u.s[t][0] = buf_u16(rs, vs[t], 0);   /* read only by the group's last step */
+                if (KS == 1 && kl + 1 == ke) u.s[t][0] = buf_u16(rs, vs[t], 0);   /* read by the group's last step */
             }
         }
-        if (++kl == steps) { kl = 0; ++gl; }
+        if (++kl == ke) { kl = ks; ++gl; }
     };
     /* Vector memory operations each load() issues after its loads into LDS (weights, scales; the
        int8 row scales, loaded on a group's last step only, are left out: a wait that counts fewer
        later loads than were issued still covers the ring). */
     constexpr int AFTER_X = NT * J + (FMT == FMT_Q4 ? (WHOLE ? 0 : 8 * NT) : 0);
     constexpr int PER_UNIT = SL + AFTER_X;                       /* plus NBD where a scale block starts */
+    /* a tile's sums times rs: lane (c, g) holds tokens 4 g .. 4 g + 3 of row c */
+    auto store = [&](int t, int64_t i0, f4_t v, float rs) {
+        const int64_t r = i0 + 16 * t + c;
+        if (r < r1) {
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int tok = 4 * g + jj;
+                if (tok < ntok)                                  /* a global (not flat) store keeps the load waits exact */
+                    as_global<g_f32*>(reinterpret_cast<char*>(d.y) + (int64_t)(token0 + tok) * d.y_stride)[r] = v[jj] * rs;
+            }
+        }
+    };
+    /* the group's sums of all waves: into LDS, joined there in wave order (tile t by wave t % KS) */
+    auto join = [&](int64_t i0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            joins[(wave * NT + t) * WAVE + lane] = __builtin_bit_cast(u32x4, acc[t]);
+            acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+        }
+        lds_barrier();
+        for (int t = wave; t < NT; t += KS) {
+            f4_t v = __builtin_bit_cast(f4_t, joins[t * WAVE + lane]);
+#pragma unroll
+            for (int p = 1; p < KS; ++p) v += __builtin_bit_cast(f4_t, joins[(p * NT + t) * WAVE + lane]);
+            float rs = 1.f;
+            if constexpr (FMT == FMT_I8)
+                if (i0 + 16 * t + c < r1) rs = f16_bits_to_f32(as_global<g_u16*>(d.s)[i0 + 16 * t + c]);
+            store(t, i0, v, rs);
+        }
+        lds_barrier();                                           /* read, before the next group's are written */
+    };
     auto multiply = [&](Unit& u, Unit& un, auto next_loaded) {   /* un: the next unit's registers */
         const int64_t i0 = r0 + gc * 16 * NT;
-        const int32_t k1 = kc + 1 == steps ? 0 : kc + 1;         /* the next unit's step, and the one after */
-        const int32_t k2 = k1 + 1 == steps ? 0 : k1 + 1;
+        const int32_t k1 = kc + 1 == ke ? ks : kc + 1;           /* the next unit's step, and the one after */
+        const int32_t k2 = k1 + 1 == ke ? ks : k1 + 1;
         /* the step's first weight, and the first one it has not already covered */
         const int64_t e0 = SHORT ? 0 : std::min<int64_t>((int64_t)kc * SK, kelem - SK), e1 = SHORT ? 0 : (int64_t)kc * SK;
 #pragma unroll
@@ -446,28 +483,26 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
                 }
             }
         }
-        if (kc + 1 == steps) {                                   /* end of a group: store, reset */
-            /* lane (c, g) holds tokens 4 g .. 4 g + 3 of row c of each tile */
+        if (kc + 1 == ke) {                                      /* end of a group: store, reset */
+            if constexpr (KS > 1) {
+                join(i0);
+            } else {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int64_t r = i0 + 16 * t + c;
-                float rs = 1.f;
-                if constexpr (FMT == FMT_I8) rs = f16_bits_to_f32((uint16_t)u.s[t][0]);
-                if constexpr (FMT == FMT_Q4) rs = Q4_UNSCALE;
-                if (r < r1) {
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const int tok = 4 * g + jj;
-                        if (tok < ntok)                          /* a global (not flat) store keeps the load waits exact */
-                            as_global<g_f32*>(reinterpret_cast<char*>(d.y) + (int64_t)(token0 + tok) * d.y_stride)[r] =
-                                acc[t][jj] * rs;
-                    }
+                for (int t = 0; t < NT; ++t) {
+                    float rs = 1.f;
+                    if constexpr (FMT == FMT_I8) rs = f16_bits_to_f32((uint16_t)u.s[t][0]);
+                    if constexpr (FMT == FMT_Q4) rs = Q4_UNSCALE;
+                    store(t, i0, acc[t], rs);
+                    acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
                 }
-                acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
             }
         }
-        if (++kc == steps) { kc = 0; ++gc; }
+        if (++kc == ke) { kc = ks; ++gc; }
     };
+    if (KS > 1 && n == 0) {                                      /* fewer steps than waves: none for this one */
+        for (int64_t g = 0; g < ngroups; ++g) join(r0 + g * 16 * NT);
+        return;
+    }
     Unit buf[2];
     const std::true_type next_loaded;
     const std::false_type last;
@@ -502,10 +537,11 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
 constexpr int mma_base_fmt(int fmt) { return fmt == FMT_Q4_WHOLE ? FMT_Q4 : fmt; }
 
 /* The matrix-core sweep over the byte range [lo, hi) of the weight stream (groups of 16 NT rows). */
-template <int FMT, int NT>
+template <int FMT, int NT, int KS>
 __device__ __forceinline__ void stream_range_mma(const DevMat* __restrict__ tab, const int64_t* __restrict__ cost,
                                                  int nmat, int64_t lo, int64_t hi, int64_t tail, int64_t main_rows,
-                                                 int32_t token0, int ntok, int lane, int& hint, u32x4* xlds) {
+                                                 int32_t token0, int ntok, int lane, int wave, int& hint, u32x4* xlds,
+                                                 u32x4* joins) {
     for (int m = first_matrix(cost, nmat, lo, hint); m < nmat; ++m) {
         const DevMat d = tab[m];
         if (d.cost0 >= hi) break;
@@ -521,7 +557,7 @@ __device__ __forceinline__ void stream_range_mma(const DevMat* __restrict__ tab,
         }
         if (rr.r0 >= rr.r1) continue;
         const bool short_rows = d.nc * 16 < 128;                 /* under one step */
-#define WSR_ROWS(F, W, SH) rows_mma<F, NT, W, SH>(d, rr.r0, rr.r1, token0, ntok, lane, xlds)
+#define WSR_ROWS(F, W, SH) rows_mma<F, NT, W, SH, KS>(d, rr.r0, rr.r1, token0, ntok, lane, wave, xlds, joins)
         const bool whole = d.nc % 8 == 0;                        /* 128-byte steps: 8 chunks or blocks */
         if constexpr (FMT == FMT_Q4_WHOLE) {                     /* the launcher checked every matrix */
             WSR_ROWS(FMT_Q4, true, false);
@@ -534,9 +570,11 @@ __device__ __forceinline__ void stream_range_mma(const DevMat* __restrict__ tab,
             else if (whole) WSR_ROWS(FMT_BF16, true, false);
             else WSR_ROWS(FMT_BF16, false, false);
         } else if ((F == 0 || F == FMT_Q4) && fmt == FMT_Q4) {
-            if (short_rows) WSR_ROWS(FMT_Q4, false, true);
-            else if (whole && (reinterpret_cast<uintptr_t>(d.s) & 15) == 0) WSR_ROWS(FMT_Q4, true, false);
-            else WSR_ROWS(FMT_Q4, false, false);
+            if constexpr (KS == 1) {                             /* (a launch that holds q4 does not split) */
+                if (short_rows) WSR_ROWS(FMT_Q4, false, true);
+                else if (whole && (reinterpret_cast<uintptr_t>(d.s) & 15) == 0) WSR_ROWS(FMT_Q4, true, false);
+                else WSR_ROWS(FMT_Q4, false, false);
+            }
         } else if ((F == 0 || F == FMT_I8) && fmt == FMT_I8) {
             if (short_rows) WSR_ROWS(FMT_I8, false, true);
             else if (whole) WSR_ROWS(FMT_I8, true, false);
