@@ -10,10 +10,11 @@
  *              synchronisation (C3, Table 1)
  *
  * Streaming layout.  HBM3E serves long sequential runs best.  Each probe block walks its own
- * contiguous region.  The 16-bit sweep hands out tiles of the weight stream (64 KiB to 2 MiB) in
+ * contiguous region.  The sweeps give each wave an equal contiguous span of the weight stream, and far
+ * more blocks than the chip holds, so that retiring blocks are replaced up to the end.  16-bit streams
+ * of 64 GiB and mixed tables hand out tiles of the stream (64 KiB to 2 MiB) in
  * order from a counter, so the waves in flight work on one moving front of memory and finish
- * together.  The q4 sweep gives each wave an equal contiguous span instead, which measured faster
- * for its heavier per-byte work; its waves keep several steps of loads in flight in registers.
+ * together.
  */
 #include <hip/hip_runtime.h>
 
@@ -438,8 +439,8 @@ static int cu_count() {
     return cache[dev];
 }
 
-/* 16-bit weights: tiles, 4 rows x 4 KiB steps per wave, one block (4 waves) per CU (few, long
-   streams).  q4: spans of about 48 KiB per wave, 8 rows x 1 block per lane per step (eight rows
+/* 16-bit weights in very long streams, and mixed tables: tiles, 4 rows x 4 KiB steps per wave, one
+   block (4 waves) per CU.  q4: spans of about 48 KiB per wave, 8 rows x 1 block per lane per step (eight rows
    share each block's activation decode), two register sets in flight; the grid is sized so that
    blocks retire and are replaced throughout the token (21,500 blocks for 4.2 GB).  int8: spans of
    about SWEEP_SPAN_I8 bytes per wave with 8 rows x 1 chunk per lane per step and three register
@@ -447,13 +448,16 @@ static int cu_count() {
    (one wave per SIMD cannot cover the latency at each row group's start). */
 constexpr int SWEEP_BLOCKS_PER_CU_16 = 1;
 constexpr int64_t SWEEP_SPAN_Q4 = 48 << 10;
-/* 16-bit streams shorter than four tiles of the largest size per wave (8 GiB with 1024 waves) go
-   over spans of about 48 KiB per wave, two rows x 8 KiB steps, instead of claimed tiles: with few
-   tiles per wave the end of the launch is uneven (the 1 GiB pass of 32 matrices of 4096 x 4096 fp16
-   measured 4.47 TB/s over tiles and 6.8 TB/s over spans), while on long streams tiles keep the
-   waves on one moving front (the 70B bf16 token measured 7.22 TB/s over tiles, 7.10 over spans). */
+/* 16-bit streams up to 64 GiB go over spans of about 48 KiB per wave, two rows x 8 KiB steps, instead
+   of claimed tiles: with few tiles per wave the end of the launch is uneven, and the blocks that
+   retire and are replaced balance it.  Measured over tiles and over spans: the 1 GiB pass of 32
+   fp16 matrices of 4096 x 4096 4.47 and 6.8 TB/s, four 70B bf16 layers and head (9 GB) 6.25 and 7.1,
+   ten layers (17 GB) 6.8 and 7.12, forty layers and head (70 GB) 7.14 and 7.15, but 78 layers
+   (136 GB) 7.15 and 6.42: over streams that long the eight contiguous parts lie far apart, and tiles
+   keep the waves on one moving front.  Spans of 24, 32, 64 and 96 KiB: 9 GB at 6.86, 6.87, 6.99 and
+   7.01 TB/s. */
 constexpr int64_t SWEEP_SPAN_16 = 48 << 10;
-constexpr int64_t SWEEP16_TILES_FROM = int64_t{8} << 30;
+constexpr int64_t SWEEP16_TILES_FROM = int64_t{64} << 30;
 constexpr int SPAN16_R = 2, SPAN16_U = 8;
 constexpr int64_t SWEEP_SPAN_I8 = 32 << 10;
 

@@ -83,3 +83,20 @@ def test_last_block_of_a_q4_row_with_an_infinite_scale():
     got = y.cpu().numpy()
     assert np.isinf(got[:, ::2]).all() and np.isfinite(got[:, 1::2]).all()
     assert np.array_equal(f32_bits(got[0]), f32_bits(got[1]))
+
+
+# 16-bit streams of over 8 GiB run over spans: table in the arguments (136 matrices) and in the
+# workspace (300), the same 64 MiB of weights in every record
+@pytest.mark.parametrize("fmt", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("n", [136, 300])
+def test_long_16bit_stream(fmt, n):
+    M, K = 4099, 8192
+    (W, _), xh = matrix(fmt, M, K, seed=n)
+    w, x = dv.to_device(W), dv.to_device(xh)
+    one = torch.full((M,), float("nan"), dtype=torch.float32, device="cuda")
+    wsr.wsr_gemv_f16(w, x, one, M, K, FMT[fmt], stream())
+    ys = torch.full((n, M + 1), float("nan"), dtype=torch.float32, device="cuda")
+    sweep([spec(fmt, M, K, w, None, x, ys[i]) for i in range(n)])
+    torch.cuda.synchronize()
+    assert torch.equal(ys[:, :M].view(torch.int32), one.view(torch.int32).expand(n, M))
+    assert torch.isnan(ys[:, M]).all()
