@@ -26,7 +26,7 @@ constexpr int64_t SWEEP_SPAN_MMA = 64 << 10;  /* least bytes of the weight strea
    1,582 -> 1,354 at 4; 72B int8 918 -> 855 and 778 -> 745; a 1.2 GB bf16 model of 2,048-wide layers
    258 -> 210; an 8B bf16 layer as a chain of four launches 289 -> 139.  With two waves 1,468, 918, 231 and
    169; with eight 1,405, 874, 227 and 143; four waves with groups of 128 rows, one wave per SIMD, 1,487,
-   843, 230 and 216.  q4 rows are short (2 to 8 KiB) and their passes bound by decoding: one wave, and
+   843, 230 and 216 (and 193 against 180 on equal int8 rows of 7,168, where one wave had 178).  q4 rows are short (2 to 8 KiB) and their passes bound by decoding: one wave, and
    one for mixed tables, which hold the q4 loops. */
 template <int FMT> constexpr int mma_split() { return FMT == FMT_F16 || FMT == FMT_BF16 || FMT == FMT_I8 ? 4 : 1; }
 
