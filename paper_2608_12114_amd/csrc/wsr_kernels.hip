@@ -418,8 +418,7 @@ static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipS
         f[i] = i < nmat ? (int)blocks : INT32_MAX;
         if (i >= nmat) continue;
         tb.m[i] = htab[i];
-        blocks += (htab[i].M + WAVES_PER_BLOCK * R - 1) / (WAVES_PER_BLOCK * R);
-        if (blocks >= INT32_MAX) return hipErrorInvalidValue;
+        blocks += (htab[i].M + WAVES_PER_BLOCK * R - 1) / (WAVES_PER_BLOCK * R);   /* at most SHORT_ROWS / 4 */
     }
     hipLaunchKernelGGL((k_sweep_short<FMT, R, U>), dim3((unsigned)blocks), dim3(BLOCK), 0, s, f[1], f[2], f[3], f[4], f[5],
                        f[6], f[7], token, tb);
@@ -518,8 +517,15 @@ static bool sweep_spans(int64_t total, int fmt_all) {
    launch) q4 1,139 and 1,395 for 32 layers and the head, int8 46.5 and 52.3 for one layer, bf16 71.7
    and 77.4; the layer as one launch (122 to 436 MB) q4 24.5 and 24.7, int8 37.2 and 38.4, bf16 equal. */
 constexpr int64_t SHORT_BYTES = 256 << 20;
-static bool sweep_short(int nmat, int64_t total, int fmt_all) {
-    return nmat <= SHORT_MATS && total <= SHORT_BYTES && fmt_all != 0;
+/* Empty rows (K = 0) cost a byte of the stream or two and could be more than a grid holds: a launch has
+   fewer than 2^32 threads, and a wave of this form takes as little as one row.  Rows that are not empty
+   stay below the limit, at 16 bytes or more each. */
+constexpr int64_t SHORT_ROWS = int64_t{1} << 24;
+static bool sweep_short(const DevMat* htab, int nmat, int64_t total, int fmt_all) {
+    if (nmat > SHORT_MATS || total > SHORT_BYTES || fmt_all == 0) return false;
+    int64_t rows = 0;
+    for (int i = 0; i < nmat; ++i) rows += htab[i].M;
+    return rows <= SHORT_ROWS;
 }
 
 /* int8 with two columns in long streams: two packed dot products per code pair are no burden to the
@@ -532,13 +538,13 @@ static bool sweep_i8_pair(const DevMat* htab, int nmat, int fmt_all, int T) {
 
 bool sweep_table_by_value(const DevMat* htab, int nmat, int64_t total, int fmt_all, int T) {
     if (T > 1 && !sweep_i8_pair(htab, nmat, fmt_all, T)) return nmat <= COLS_TABLE_ARG;
-    return (T == 1 && sweep_short(nmat, total, fmt_all)) || (nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all));
+    return (T == 1 && sweep_short(htab, nmat, total, fmt_all)) || (nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all));
 }
 
 hipError_t launch_sweep(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total,
                         int fmt_all, int32_t token, int T, unsigned* ctr, hipStream_t s) {
     if (nmat == 0 || total == 0) return hipSuccess;
-    if (T == 1 && sweep_short(nmat, total, fmt_all)) {
+    if (T == 1 && sweep_short(htab, nmat, total, fmt_all)) {
         switch (fmt_all) {
             case FMT_Q4: return launch_short<FMT_Q4, 4, 1>(htab, nmat, token, s);
             case FMT_I8: return launch_short<FMT_I8, 2, 1>(htab, nmat, token, s);
