@@ -169,6 +169,9 @@ __device__ __forceinline__ u32x4 keep_if(bool ok, u32x4 v) { return ok ? v : zer
    17.8k tok/s; at 4 tokens 4.4k -> 4.9k).  mma_ring_slots counts the ring's slots of 64 chunks of 16 bytes: the two units'
    activations, then (q4) one block of scales for row groups of NT tiles. */
 constexpr int MMA_SCALE_STEPS = 4;
+
+/* Parts in which the steps of a 16-bit or int8 row are summed. */
+constexpr int MMA_SPLIT = 4;
 template <int FMT, int NT>
 constexpr int mma_ring_slots() { return 2 * MmaStep<FMT>::SLABS + (FMT == FMT_Q4 ? NT : 0); }
 
@@ -202,7 +205,9 @@ __device__ __forceinline__ void wait_vm() {
    ring to the weights.
    With KS > 1 the KS waves of a workgroup take the same rows and split their steps: wave p the steps
    [p steps / KS, (p + 1) steps / KS), and at a group's end they join their sums through LDS (joins:
-   NT KiB per wave), in wave order, each wave storing some of the tiles. */
+   NT KiB per wave), in wave order, each wave storing some of the tiles.  A wave alone (KS = 1, in
+   tables of several formats) sums 16-bit and int8 rows in the same MMA_SPLIT parts and joins them in the
+   same order, so that a matrix's outputs do not depend on what else its table holds. */
 template <int FMT, int NT, bool WHOLE, bool SHORT, int KS>
 __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1, int32_t token0, int ntok, int lane,
                                          int wave, u32x4* __restrict__ xlds, u32x4* __restrict__ joins) {
@@ -219,12 +224,21 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
     const int32_t ks = KS == 1 ? 0 : (int32_t)((int64_t)steps * wave / KS);          /* this wave's steps */
     const int32_t ke = KS == 1 ? steps : (int32_t)((int64_t)steps * (wave + 1) / KS);
     const int64_t n = ngroups * (ke - ks);                       /* units */
-    if (KS == 1 && n == 0) return;
     const rsrc_t rx = buffer_of(uniform_ptr(static_cast<const char*>(d.x) + (int64_t)token0 * d.x_stride));
     const int64_t srow = FMT == FMT_Q4 ? nc * 2 : 2;             /* scale bytes per row */
     f4_t acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+    constexpr bool PARTS = KS == 1 && FMT != FMT_Q4;
+    f4_t sum[PARTS ? NT : 1];                                    /* the parts before the current one */
+#pragma unroll
+    for (int t = 0; t < (PARTS ? NT : 1); ++t) sum[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+    auto part_end = [&](int32_t k) {                             /* of the part that holds step k (steps: at most 2^19) */
+        int32_t p = 1;
+        while (p < MMA_SPLIT && steps * p / MMA_SPLIT <= k) ++p;
+        return steps * p / MMA_SPLIT;
+    };
+    int32_t pend = PARTS ? part_end(0) : 0;
     int64_t gl = 0, gc = 0;                                      /* group of the next unit to load, multiply */
     int32_t kl = ks, kc = ks;                                    /* and its step                             */
     int lbuf = 0, mbuf = 0;                                      /* LDS ring half of the next load, multiply */
@@ -483,6 +497,16 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
                 }
             }
         }
+        if constexpr (PARTS) {
+            if (kc + 1 == pend) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    sum[t] += acc[t];
+                    acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+                }
+                pend = part_end(kc + 1 == ke ? 0 : kc + 1);
+            }
+        }
         if (kc + 1 == ke) {                                      /* end of a group: store, reset */
             if constexpr (KS > 1) {
                 join(i0);
@@ -492,8 +516,9 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
                     float rs = 1.f;
                     if constexpr (FMT == FMT_I8) rs = f16_bits_to_f32((uint16_t)u.s[t][0]);
                     if constexpr (FMT == FMT_Q4) rs = Q4_UNSCALE;
-                    store(t, i0, acc[t], rs);
-                    acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+                    f4_t& v = PARTS ? sum[PARTS ? t : 0] : acc[t];
+                    store(t, i0, v, rs);
+                    v = f4_t{0.f, 0.f, 0.f, 0.f};
                 }
             }
         }

@@ -28,7 +28,7 @@ constexpr int64_t SWEEP_SPAN_MMA = 64 << 10;  /* least bytes of the weight strea
    169; with eight 1,405, 874, 227 and 143; four waves with groups of 128 rows, one wave per SIMD, 1,487,
    843, 230 and 216 (and 193 against 180 on equal int8 rows of 7,168, where one wave had 178).  q4 rows are short (2 to 8 KiB) and their passes bound by decoding: one wave, and
    one for mixed tables, which hold the q4 loops. */
-template <int FMT> constexpr int mma_split() { return FMT == FMT_F16 || FMT == FMT_BF16 || FMT == FMT_I8 ? 4 : 1; }
+template <int FMT> constexpr int mma_split() { return FMT == FMT_F16 || FMT == FMT_BF16 || FMT == FMT_I8 ? MMA_SPLIT : 1; }
 
 /* Workgroups of mma_split(FMT) waves, few so that one whose span holds no row group frees its slots
    at once.  Workgroups w < w1 split the stream's bytes [0, tail) into equal spans of whole row groups

@@ -3,12 +3,16 @@ fewer steps than waves (some waves have none), of uneven shares and with a ragge
 several row groups with a ragged last one, several matrices in one call and the outputs' bounds."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import synth
+from synth import device as dv
 from synth import workloads as wl
-from gpu_util import needs_gpu, rel_l2
-from test_gpu_mma import TOL, host_matrix, run_mma
+from gpu_util import f32_bits, needs_gpu, rel_l2, stream, zeros_u8
+from test_gpu_mma import CODE, TOL, host_matrix, run_mma
+
+from paper_2608_12114_amd import wsr
 
 pytestmark = [pytest.mark.gpu, needs_gpu]
 
@@ -28,3 +32,28 @@ def test_split_steps(fmt, steps, ragged):
     for t in range(T):
         want = ora.gemv(dict(fmt=fmt, w=W, s=S), X[t]) if fmt == wl.I8 else ora.gemv16(W, X[t], fmt)
         assert rel_l2(y[t, :M], want) <= TOL, (fmt, K, t)
+
+
+def mma_table(entries, T):
+    """Outputs of one call over [(fmt, M, K, w, s, x)], each (T, M)."""
+    ys = [torch.full((T, M), float("nan"), dtype=torch.float32, device="cuda") for _, M, *_ in entries]
+    mats = wsr.make_mats([dict(fmt=CODE[f], M=M, K=K, w=w, scales=s, x=x, x_tok_stride=2 * K, y=y, y_tok_stride=4 * M)
+                          for (f, M, K, w, s, x), y in zip(entries, ys)])
+    ws = zeros_u8(wsr.wsr_sweep_workspace_bytes(mats))
+    wsr.wsr_decode_sweep_mma(mats, T, ws, ws.numel(), stream())
+    return [f32_bits(y.cpu().numpy()) for y in ys]
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 9, 30])
+@pytest.mark.parametrize("ragged", [0, 16, -48], ids=["whole", "longer", "shorter"])
+def test_outputs_do_not_depend_on_the_rest_of_the_table(steps, ragged):
+    """A matrix's outputs are the same bits alone, and in a table that holds other formats too, where one
+    wave takes the rows that four share when all are of one format."""
+    T, entries = 5, []
+    for i, fmt in enumerate((wl.F16, wl.I8, wl.Q4, wl.BF16)):
+        M, K = 150 + 7 * i, {wl.Q4: 256}.get(fmt, STEP.get(fmt)) * steps + (32 if fmt == wl.Q4 and ragged else ragged)
+        W, S = host_matrix(fmt, M, K, seed=37 + i)
+        X = synth.normal16((T, K), wl.X_SIGMA, wl.BF16 if fmt == wl.BF16 else wl.F16, seed=37 + i, stream=632)
+        entries.append((fmt, M, K, dv.to_device(W), None if S is None else dv.to_device(S), dv.to_device(X)))
+    for e, got in zip(entries, mma_table(entries, T)):
+        assert np.array_equal(got, mma_table([e], T)[0]), (e[0], e[2])
