@@ -2,8 +2,8 @@
  * wsr_kernels.hip - HIP kernels of the weight-streaming read path for gfx950 and their launchers.
  *
  *  k_probe_part / k_probe_final   pure-read reference: fp32 buffer -> fp64 sum (paper Sec. 3.1, 3.3)
- *  k_gemv16    single-token GEMV, fp16 / bf16 weights and activations, fp32 accumulate (Sec. 3.1)
- *  k_gemv_q4   single-token GEMV over 4-bit block-quantised weights, decoded in registers
+ *  k_gemv      single-token GEMV, fp32 accumulate: fp16 / bf16 weights (Sec. 3.1), 4-bit blocks and int8
+ *              rows decoded in registers; k_gemv_small the same for the smallest matrices
  *  k_sweep     one decode token: every matrix of a table in one persistent launch (Sec. 6.2)
  *  k_put_table writes the sweep's matrix table into the caller's workspace from kernel arguments
  *              and clears the sweep's tile counters, so a sweep needs no host copy or host
@@ -119,63 +119,83 @@ hipError_t launch_probe(const float* buf, int64_t n, double* sum_dev, void* ws, 
 
 /* ======================================= GEMVs ================================================ */
 
-/* A GEMV's matrix travels as single arguments, which the command processor puts into registers before
-   the first instruction (the build asks for 16 of them; a structure by value stays in memory): the
-   loads of the weights then wait for nothing. */
-#define WSR_GEMV_ARGS const void *w, const void *sc, const void *x, float *y, int64_t M, int64_t nc
-__device__ __forceinline__ DevMat gemv_mat(WSR_GEMV_ARGS) {
+/* One group of ROWS rows of a matrix, by one wave. */
+template <int FMT, int R, int U>
+struct Gemv16 {
+    static constexpr int ROWS = R;
+    static __device__ __forceinline__ void run(const DevMat& d, int64_t r0, int lane) {
+        rows16<FMT, R, U>(d, r0, std::min<int64_t>(r0 + R, d.M), 0, lane);
+    }
+};
+template <int R, int U>
+struct GemvQ4 {
+    static constexpr int ROWS = R;
+    static __device__ __forceinline__ void run(const DevMat& d, int64_t r0, int lane) {
+        rows_q4<R, U>(d, r0, std::min<int64_t>(r0 + R, d.M), 0, lane);
+    }
+};
+/* The full and the partial group take separate branches rather than a clamp of the row end: the clamp's
+   select was miscompiled (the pre-emit peephole dropped the instruction that set the select's
+   condition, so the end became r0 + R past the last row). */
+struct GemvI8 {
+    static constexpr int ROWS = I8_GEMV_R;
+    static __device__ __forceinline__ void run(const DevMat& d, int64_t r0, int lane) {
+        if (d.M - r0 >= ROWS) rows_i8<ROWS>(d, r0, r0 + ROWS, 0, lane);
+        else rows_i8<1>(d, r0, d.M, 0, lane);
+    }
+};
+template <typename G>
+__device__ __forceinline__ void gemv_wave(const DevMat& d) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t r0 = ((int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block()) * G::ROWS;
+    if (r0 < d.M) G::run(d, r0, lane);
+}
+
+/* The matrix as single arguments, which the command processor puts into registers before the first
+   instruction (the build asks for 16 of them): a launch among others takes 0.2 to 0.25 us less
+   than with one structure, which is read from the argument memory (us, this and that: f16 4096 x 4096
+   6.35 and 6.57, q4 4.00 and 4.20, int8 12288 x 7168 14.80 and 15.07).  The addresses go as integers:
+   the runtime looks up the allocation of every pointer argument (3.26 us of host time per call against
+   3.33, as one structure 3.15). */
+template <typename G>
+__global__ __launch_bounds__(BLOCK) void k_gemv(uint64_t w, uint64_t s, uint64_t x, uint64_t y, int64_t M, int64_t nc) {
     DevMat d{};
-    d.w = w;
-    d.s = sc;
-    d.x = x;
-    d.y = y;
+    d.w = reinterpret_cast<const void*>(w);
+    d.s = reinterpret_cast<const void*>(s);
+    d.x = reinterpret_cast<const void*>(x);
+    d.y = reinterpret_cast<float*>(y);
     d.M = M;
     d.nc = nc;
-    return d;
+    gemv_wave<G>(d);
 }
-#define WSR_GEMV_MAT const DevMat d = gemv_mat(w, sc, x, y, M, nc)
+/* The matrix as one structure: where the GPU is done before the host has enqueued the next call, the
+   cheaper call is the faster one. */
+template <typename G>
+__global__ __launch_bounds__(BLOCK) void k_gemv_small(DevMat d) { gemv_wave<G>(d); }
 
-/* One wave per R consecutive rows. */
-template <int FMT, int R, int U>
-__global__ __launch_bounds__(BLOCK) void k_gemv16(WSR_GEMV_ARGS) {
-    WSR_GEMV_MAT;
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
-    const int64_t r0 = wave * R;
-    if (r0 >= d.M) return;
-    rows16<FMT, R, U>(d, r0, std::min<int64_t>(r0 + R, d.M), 0, lane);
-}
-
-template <int R, int U>
-__global__ __launch_bounds__(BLOCK) void k_gemv_q4(WSR_GEMV_ARGS) {
-    WSR_GEMV_MAT;
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
-    const int64_t r0 = wave * R;
-    if (r0 >= d.M) return;
-    rows_q4<R, U>(d, r0, std::min<int64_t>(r0 + R, d.M), 0, lane);
+/* Calls that the host bounds: those the GPU takes less than about 2.8 us for, with rows of one or two
+   steps of a wave.  us a call back to back, as a structure and as single arguments: bf16 256 x 4096 2.95 and
+   3.09, 768 x 4096 3.00 and 3.13, 512 x 2048 2.92 and 3.08, 2048 x 512 2.96 and 3.11, but 1536 x
+   2048 3.38 and 3.09, 32 x 8192 3.30 and 3.13; q4 2048 x 2048 2.94 and 3.07, 256 x 4096 3.12 and
+   3.09 to 3.18 and 3.27, but 8192 x 512 3.52 and 3.28, 1024 x 4096 3.83 and 3.58; int8 2048 x 1024
+   2.96 and 3.09, 256 x 2048 2.96 and 3.12, but 1024 x 2048 3.54 and 3.27. */
+static bool gemv_small(const DevMat& m) {
+    const int64_t bytes = m.M * m.row_bytes;
+    if (m.fmt == FMT_F16 || m.fmt == FMT_BF16) return m.nc <= 512 && (m.M <= 1024 || bytes <= (2 << 20));
+    return m.nc <= 128 && bytes <= (m.nc <= 64 ? 2 << 20 : 1 << 20);
 }
 
-template <typename K>
-static hipError_t launch_rows(K kernel, const DevMat& m, int R, hipStream_t s) {
-    const int64_t waves = (m.M + R - 1) / R;
-    const int64_t blocks = (waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(BLOCK), 0, s, m.w, m.s, m.x, m.y, m.M, m.nc);
+template <typename G>
+static hipError_t launch_rows(const DevMat& m, hipStream_t s) {
+    const int64_t waves = (m.M + G::ROWS - 1) / G::ROWS;
+    const dim3 grid((unsigned)((waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK));
+    if (gemv_small(m))
+        hipLaunchKernelGGL((k_gemv_small<G>), grid, dim3(BLOCK), 0, s, m);
+    else
+        hipLaunchKernelGGL((k_gemv<G>), grid, dim3(BLOCK), 0, s, reinterpret_cast<uint64_t>(m.w),
+                           reinterpret_cast<uint64_t>(m.s), reinterpret_cast<uint64_t>(m.x),
+                           reinterpret_cast<uint64_t>(m.y), m.M, m.nc);
     return hipGetLastError();
-}
-
-/* One group of R rows per wave.  The full and the partial group take separate branches rather than
-   a clamp of the row end: the clamp's select was miscompiled (the pre-emit peephole dropped the
-   instruction that set the select's condition, so the end became r0 + R past the last row). */
-__global__ __launch_bounds__(BLOCK) void k_gemv_i8(WSR_GEMV_ARGS) {
-    WSR_GEMV_MAT;
-    constexpr int R = I8_GEMV_R;
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave_in_block();
-    const int64_t r0 = wave * R;
-    if (r0 >= d.M) return;
-    if (d.M - r0 >= R) rows_i8<R>(d, r0, r0 + R, 0, lane);
-    else rows_i8<1>(d, r0, d.M, 0, lane);
 }
 
 /* Two columns of a 16-bit matrix on the vector ALUs, four rows per wave. */
@@ -230,16 +250,16 @@ hipError_t launch_gemv(const DevMat& m, hipStream_t s) {
     if (m.M == 0) return hipSuccess;
     switch (m.fmt) {
         case FMT_F16:
-            return gemv16_long_rows(m) ? launch_rows(k_gemv16<FMT_F16, 4, 8>, m, 4, s)
-                                       : launch_rows(k_gemv16<FMT_F16, 1, 8>, m, 1, s);
+            return gemv16_long_rows(m) ? launch_rows<Gemv16<FMT_F16, 4, 8>>(m, s)
+                                       : launch_rows<Gemv16<FMT_F16, 1, 8>>(m, s);
         case FMT_BF16:
-            return gemv16_long_rows(m) ? launch_rows(k_gemv16<FMT_BF16, 4, 8>, m, 4, s)
-                                       : launch_rows(k_gemv16<FMT_BF16, 1, 8>, m, 1, s);
+            return gemv16_long_rows(m) ? launch_rows<Gemv16<FMT_BF16, 4, 8>>(m, s)
+                                       : launch_rows<Gemv16<FMT_BF16, 1, 8>>(m, s);
         case FMT_Q4:
-            return m.nc >= 256 ? launch_rows(k_gemv_q4<2, 2>, m, 2, s)
-                               : launch_rows(k_gemv_q4<4, 1>, m, 4, s);
+            return m.nc >= 256 ? launch_rows<GemvQ4<2, 2>>(m, s)
+                               : launch_rows<GemvQ4<4, 1>>(m, s);
         case FMT_I8:
-            return launch_rows(k_gemv_i8, m, I8_GEMV_R, s);
+            return launch_rows<GemvI8>(m, s);
         default:
             return hipErrorInvalidValue;
     }
