@@ -13,7 +13,15 @@
 
 namespace wsr {
 
-/* A table by value: the kernel's arguments, or (N = 0) pointers to the table in device memory. */
+/* A table by value: the kernel's arguments, or (N = 0) pointers to the table in device memory.  q4 and int8
+   passes take up to COLS_TABLE_ARG_MAX matrices by value, in the sizes of the single-token sweep: the
+   upload before them costs 2 to 3 us (us a pass at 8 columns, uploaded and by value: nine q4 4096 x
+   4096 37.1 and 34.2, 28 int8 1024 x 1024 14.8 and 11.6, twelve int8 12288 x 7168 221 and 220, the
+   8B q4 model 1,107 and 1,104). */
+constexpr int COLS_TABLE_ARG = 8, COLS_TABLE_ARG_MID = 32, COLS_TABLE_ARG_MAX = 288;
+int cols_table_by_value(int fmt_all) {
+    return fmt_all == FMT_Q4 || fmt_all == FMT_I8 ? COLS_TABLE_ARG_MAX : COLS_TABLE_ARG;
+}
 template <int N>
 struct ColsTable {
     DevMat m_[N];
@@ -21,6 +29,7 @@ struct ColsTable {
     __device__ const DevMat* m() const { return m_; }
     __device__ const int64_t* cost() const { return cost_; }
 };
+static_assert(sizeof(ColsTable<COLS_TABLE_ARG_MAX>) + 64 <= 32000, "the by-value table must stay within the checked argument size");
 template <>
 struct ColsTable<0> {
     const DevMat* __restrict__ m_;
@@ -131,7 +140,7 @@ static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int n
             constexpr int RG = split_rg<FMT>();
             /* us, with two and with four groups per round: q4 at 8 columns 1024 x 4096 6.1 and 7.2, 4096 x
                4096 8.8 and 7.4 */
-            if constexpr (N > 0 && RG > SPLIT_RG_FEW)
+            if constexpr (N == COLS_TABLE_ARG && RG > SPLIT_RG_FEW)
                 if (rounds_of(htab, nmat, 4 * RG) <= 128)
                     return launch_split<FMT, TQ, SPLIT_RG_FEW, N>(tb, htab, nmat, total, token, T, s);
             return launch_split<FMT, TQ, RG, N>(tb, htab, nmat, total, token, T, s);
@@ -152,16 +161,25 @@ static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int n
     return hipErrorInvalidValue;
 }
 
-template <int FMT, int TQ>
-static hipError_t launch_q(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total,
-                           int32_t token, int T, hipStream_t s) {
-    if (nmat > COLS_TABLE_ARG) return launch_table<FMT, TQ, 0>({tab, cost}, htab, nmat, total, token, T, s);
-    ColsTable<COLS_TABLE_ARG> tb;
+template <int FMT, int TQ, int N>
+static hipError_t launch_arg(const DevMat* htab, int nmat, int64_t total, int32_t token, int T, hipStream_t s) {
+    ColsTable<N> tb;
     for (int i = 0; i < nmat; ++i) {
         tb.m_[i] = htab[i];
         tb.cost_[i] = htab[i].cost0;
     }
-    return launch_table<FMT, TQ, COLS_TABLE_ARG>(tb, htab, nmat, total, token, T, s);
+    return launch_table<FMT, TQ, N>(tb, htab, nmat, total, token, T, s);
+}
+
+template <int FMT, int TQ>
+static hipError_t launch_q(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total,
+                           int32_t token, int T, hipStream_t s) {
+    if (nmat <= COLS_TABLE_ARG) return launch_arg<FMT, TQ, COLS_TABLE_ARG>(htab, nmat, total, token, T, s);
+    if constexpr (FMT == FMT_Q4 || FMT == FMT_I8) {
+        if (nmat <= COLS_TABLE_ARG_MID) return launch_arg<FMT, TQ, COLS_TABLE_ARG_MID>(htab, nmat, total, token, T, s);
+        if (nmat <= COLS_TABLE_ARG_MAX) return launch_arg<FMT, TQ, COLS_TABLE_ARG_MAX>(htab, nmat, total, token, T, s);
+    }
+    return launch_table<FMT, TQ, 0>({tab, cost}, htab, nmat, total, token, T, s);
 }
 
 template <int FMT>

@@ -51,10 +51,10 @@ hipError_t launch_sweep(const DevMat* tab, const int64_t* cost, const DevMat* ht
                         int fmt_all, int32_t token, int T, unsigned* ctr, hipStream_t s);
 /* Tokens (or columns) token .. token + T - 1 (2 <= T <= 16, at most 8 with a q4 or int8 matrix) in one
    pass over the weights, each bit for bit the single-token result.  htab: the table on the host; with
-   at most COLS_TABLE_ARG matrices it goes by value, else the kernels read tab and cost.  Every nc is
+   at most cols_table_by_value(fmt_all) matrices it goes by value, else the kernels read tab and cost.  Every nc is
    at most COLS_MAX_NC: the kernels address sixteen rows with 32-bit offsets (rows of up to 256 MiB;
    the callers take longer rows column by column, whose results are the same bits). */
-constexpr int COLS_TABLE_ARG = 8;
+int cols_table_by_value(int fmt_all);
 constexpr int64_t COLS_MAX_NC = (int64_t{1} << 24) - 1;
 hipError_t launch_cols(const DevMat* tab, const int64_t* cost, const DevMat* htab, int nmat, int64_t total_bytes,
                        int fmt_all, int32_t token, int T, hipStream_t s);

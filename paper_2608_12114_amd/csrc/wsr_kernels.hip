@@ -557,7 +557,7 @@ static bool sweep_i8_pair(const DevMat* htab, int nmat, int fmt_all, int T) {
 }
 
 bool sweep_table_by_value(const DevMat* htab, int nmat, int64_t total, int fmt_all, int T) {
-    if (T > 1 && !sweep_i8_pair(htab, nmat, fmt_all, T)) return nmat <= COLS_TABLE_ARG;
+    if (T > 1 && !sweep_i8_pair(htab, nmat, fmt_all, T)) return nmat <= cols_table_by_value(fmt_all);
     return (T == 1 && sweep_short(htab, nmat, total, fmt_all)) || (nmat <= TABLE_ARG_MAX && sweep_spans(total, fmt_all));
 }
 

@@ -86,11 +86,13 @@ def test_two_columns(fmt, T, M):
         assert np.array_equal(f32_bits(one), f32_bits(y[:, :M])) and np.isnan(y[:, M:]).all()
 
 
-def test_one_pass_over_matrices_sharing_activations():
-    """Runs of matrices with one activation, with another and with another length in one table, more of
-    them than the launch arguments hold; batch 8, 13 tokens (passes of 8, 4 and 1)."""
+@pytest.mark.parametrize("n", [8, 9, 32, 33, 40, 288, 289])
+def test_one_pass_over_matrices_sharing_activations(n):
+    """Runs of matrices with one activation, with another and with another length in one table, as many
+    as each size of the launch arguments holds and one more; batch 8, 13 tokens (passes of 8, 4 and
+    1)."""
     specs, outs = [], []
-    shapes = [(700, 512), (100, 512), (300, 2048), (50, 544)] * 10
+    shapes = ([(700, 512), (100, 512), (300, 2048), (50, 544)] * 73)[:n]
     xs = {K: dv.to_device(synth.normal16((13, K), wl.X_SIGMA, wl.F16, seed=K, stream=704)) for K in (512, 2048, 544)}
     for i, (M, K) in enumerate(shapes):
         W, S = matrix(wl.Q4, M, K, seed=i)
