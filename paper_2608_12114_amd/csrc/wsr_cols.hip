@@ -82,18 +82,22 @@ static int64_t rounds_of(const DevMat* m, int nmat, int64_t rows) {
 }
 
 /* Whether a pass takes k_split.  k_cols needs its rounds of 32 rows to fill the 512 workgroups the
-   chip holds: with fewer, and so with parts of the chip idle, the split form's smaller rounds win
-   (in us, k_split against k_cols and against the vector-ALU form before both: q4 at 8 columns
-   4096 x 4096 7.6, 11.6, 11.9; 4096 x 14336 15.2, 29.4, 35.1; 28672 x 4096 (896 rounds) 39.1, 25.2,
-   77.7; int8 at 4 columns 12288 x 7168 (384 rounds) 18.5, 22.5, 23.3, at 8 columns 25.7, 24.5, 37.1;
-   bf16 8192 x 8192 (256 rounds) at 8 columns 27.9, 34.1, 34.7, at 16 35.2, 36.5, 38.9).  16-bit
-   weights with at most four columns, whose activations are half their weights' size or less, stay
+   chip holds: with fewer, and so with parts of the chip idle, the split form's smaller rounds win.  us,
+   k_split and k_cols, at K = 4096 / 14336 (16 columns: / 7168):
+     rounds            192                    256                    384                    448                    512
+     q4   2 columns   7.6 8.4 / 15.4 19.0    7.7 8.6 / 16.5 19.6    9.9 11.0 / 23.1 26.8   11.9 11.1 / 27.5 27.4  13.4 11.2 / 28.4 28.2
+     q4   8 columns  10.4 11.3 / 22.6 29.5  10.6 11.6 / 23.8 29.6  14.4 15.7 / 34.0 41.0  17.0 15.8 / 41.3 41.9  17.4 16.1 / 43.1 43.5
+     int8 4 columns   9.1 11.3 / 20.1 27.2  10.7 12.7 / 21.5 28.3  13.5 15.0 / 31.7 35.4  15.4 15.8 / 39.2 37.0  16.1 17.5 / 40.9 39.4
+     int8 8 columns  10.5 11.6 / 24.5 27.7  11.9 12.8 / 26.6 30.6  16.1 16.5 / 39.0 42.7  19.2 17.4 / 48.0 45.3  21.5 19.1 / 52.9 48.6
+     bf16 8 columns  13.4 17.3 / 36.1 44.1  17.6 21.7 / 47.9 47.6  21.2 28.3 / 67.6 69.2  26.1 29.4 / 87.6 76.5  27.3 34.3 / 91.0 88.1
+     bf16 16 columns 16.4 18.6 / 25.7 25.7  23.9 22.6 / 37.4 26.9  27.8 28.9 / 46.4 39.1  40.4 29.1 / 68.1 41.1  41.6 37.5 / 70.5 44.3
+   16-bit weights with at most four columns, whose activations are half their weights' size or less, stay
    with the split form on long streams too (four layers and the head of the 70B model in bf16 at 2
-   columns: 1.37, 1.46, 1.47 ms per pass, at 4 1.38, 1.46, 1.51). */
+   columns: 1.37, 1.46 ms per pass, at 4 1.38, 1.46). */
 static bool cols_split(int fmt, int T, int64_t rounds32) {
     const bool w16 = fmt == FMT_F16 || fmt == FMT_BF16;
     if (w16 && T <= 4) return true;
-    return rounds32 < (T > 8 ? 256 : fmt == FMT_I8 && T <= 4 ? 512 : 384);
+    return T > 8 ? rounds32 < 256 : rounds32 <= (fmt == FMT_I8 && T <= 4 ? 512 : 384);
 }
 
 bool cols_takes_split(const DevMat* htab, int nmat, int fmt_all, int T) {
