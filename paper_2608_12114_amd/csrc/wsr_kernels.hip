@@ -185,17 +185,36 @@ static bool gemv_small(const DevMat& m) {
     return m.nc <= 128 && bytes <= (m.nc <= 64 ? 2 << 20 : 1 << 20);
 }
 
+/* Rows [r0, M) of a matrix of the single-column kernels' layout. */
+static DevMat rows_from(const DevMat& m, int64_t r0) {
+    DevMat d = m;
+    d.w = static_cast<const char*>(m.w) + r0 * m.nc * 16;
+    if (m.s) d.s = static_cast<const char*>(m.s) + r0 * (m.fmt == FMT_Q4 ? m.nc * 2 : 2);
+    d.y = m.y + r0;
+    d.M = m.M - r0;
+    return d;
+}
+
+/* A launch holds fewer than 2^32 threads: matrices of more rows than the waves of 2^23 blocks take go in
+   several (16-bit ones from 2^25 rows on). */
+constexpr int64_t GEMV_BLOCKS = int64_t{1} << 23;
 template <typename G>
 static hipError_t launch_rows(const DevMat& m, hipStream_t s) {
-    const int64_t waves = (m.M + G::ROWS - 1) / G::ROWS;
-    const dim3 grid((unsigned)((waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK));
-    if (gemv_small(m))
-        hipLaunchKernelGGL((k_gemv_small<G>), grid, dim3(BLOCK), 0, s, m);
-    else
-        hipLaunchKernelGGL((k_gemv<G>), grid, dim3(BLOCK), 0, s, reinterpret_cast<uint64_t>(m.w),
-                           reinterpret_cast<uint64_t>(m.s), reinterpret_cast<uint64_t>(m.x),
-                           reinterpret_cast<uint64_t>(m.y), m.M, m.nc);
-    return hipGetLastError();
+    constexpr int64_t each = WAVES_PER_BLOCK * G::ROWS;
+    for (int64_t r0 = 0; r0 < m.M; r0 += GEMV_BLOCKS * each) {
+        DevMat d = r0 ? rows_from(m, r0) : m;
+        d.M = std::min<int64_t>(d.M, GEMV_BLOCKS * each);
+        const dim3 grid((unsigned)((d.M + each - 1) / each));
+        if (gemv_small(d))
+            hipLaunchKernelGGL((k_gemv_small<G>), grid, dim3(BLOCK), 0, s, d);
+        else
+            hipLaunchKernelGGL((k_gemv<G>), grid, dim3(BLOCK), 0, s, reinterpret_cast<uint64_t>(d.w),
+                               reinterpret_cast<uint64_t>(d.s), reinterpret_cast<uint64_t>(d.x),
+                               reinterpret_cast<uint64_t>(d.y), d.M, d.nc);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 /* Two columns of a 16-bit matrix on the vector ALUs, four rows per wave. */
@@ -222,7 +241,8 @@ static hipError_t launch_gemv16_pair(const DevMat& m, hipStream_t s) {
    1,024 f16 8.1 and 10.5, 20,000 x 4,096 27.4 and 29.2, 100,000 x 4,096 bf16 121 and 128; 8,192 x
    8,192 29.8 and 25.2). */
 static bool gemv16_pair(const DevMat& m, int T) {
-    return T == 2 && (m.fmt == FMT_F16 || m.fmt == FMT_BF16) && m.M >= 4 * 4 * 1024;
+    return T == 2 && (m.fmt == FMT_F16 || m.fmt == FMT_BF16) && m.M >= 4 * 4 * 1024 &&
+           m.M <= GEMV_BLOCKS * WAVES_PER_BLOCK * PAIR16_R;     /* more than a launch holds */
 }
 
 hipError_t launch_gemv_cols(const DevMat& m, int T, hipStream_t s) {

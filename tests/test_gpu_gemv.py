@@ -159,3 +159,42 @@ def test_gemv_q4_identity_blocks():
     S = np.full((K, K // 32), one, np.uint16)
     x = synth.normal16(K, 1.0, "f16", seed=4, stream=206)
     assert rel_l2(gemvq4(Wq, S, x, K, K), x.view(np.float16).astype(np.float64)) <= TOL / 100
+
+
+@pytest.mark.parametrize("fmt,M,K", [(wsr.WSR_F16, (1 << 26) + 5, 8), (wsr.WSR_BF16, (1 << 25) + 3, 0), (wsr.WSR_F16, 1 << 25, 8),
+                                     (wsr.WSR_Q4, (1 << 27) + 9, 32), (wsr.WSR_I8, (1 << 27) + 9, 16)])
+def test_more_rows_than_one_launch_holds(fmt, M, K):
+    """A launch holds fewer than 2^32 threads: matrices of more rows go in several launches.  Rows at the
+    ends and at the seams equal the same rows as a matrix of their own, single and as columns."""
+    nb = {wsr.WSR_Q4: K // 2, wsr.WSR_I8: K}.get(fmt, 2 * K)
+    sb = {wsr.WSR_Q4: K // 16, wsr.WSR_I8: 2}.get(fmt, 0)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    w = torch.randint(0, 48, (max(16, M * nb),), dtype=torch.uint8, device="cuda", generator=g)    # 16-bit: finite values
+    s = torch.randint(0, 48, (max(16, M * sb),), dtype=torch.uint8, device="cuda", generator=g)
+    x = torch.ones(max(8, K), device="cuda").to(torch.bfloat16 if fmt == wsr.WSR_BF16 else torch.float16)
+    y = torch.full((2, M + 4), 7.0, dtype=torch.float32, device="cuda")
+
+    def gemv(r0, rows, out, columns):
+        wp, sp = w.data_ptr() + r0 * nb, s.data_ptr() + r0 * sb
+        if fmt in (wsr.WSR_F16, wsr.WSR_BF16):
+            if columns:
+                wsr.wsr_gemv_f16_cols(wp, x, 0, out, 0, rows, K, 1, fmt, stream())
+            else:
+                wsr.wsr_gemv_f16(wp, x, out, rows, K, fmt, stream())
+        elif columns:
+            (wsr.wsr_gemv_q4_cols if fmt == wsr.WSR_Q4 else wsr.wsr_gemv_i8_cols)(wp, sp, x, 0, out, 0, rows, K, 1, stream())
+        else:
+            (wsr.wsr_gemv_q4 if fmt == wsr.WSR_Q4 else wsr.wsr_gemv_i8)(wp, sp, x, out, rows, K, stream())
+
+    gemv(0, M, y[0], False)
+    gemv(0, M, y[1], True)
+    assert torch.equal(y[0].view(torch.int32), y[1].view(torch.int32))
+    assert (y[:, M:] == 7.0).all().item() and not (y[0, :M] == 7.0).all().item()
+    seam = [1 << e for e in (24, 25, 26, 27) if (1 << e) < M]
+    for at in [0, M - 64] + [r - 64 for r in seam]:
+        n = min(128, M - at)
+        part = torch.full((n,), 7.0, dtype=torch.float32, device="cuda")
+        gemv(at, n, part, False)
+        assert torch.equal(part.view(torch.int32), y[0, at:at + n].view(torch.int32)), at
+    del w, s, y
+    torch.cuda.empty_cache()
