@@ -170,8 +170,13 @@ __device__ __forceinline__ u32x4 keep_if(bool ok, u32x4 v) { return ok ? v : zer
    activations, then (q4) one block of scales for row groups of NT tiles. */
 constexpr int MMA_SCALE_STEPS = 4;
 
-/* Parts in which the steps of a 16-bit or int8 row are summed. */
-constexpr int MMA_SPLIT = 4;
+/* Parts in which the steps of a 16-bit or int8 row are summed.  Rows of a multiple of MMA_TURN_BYTES begin
+   each part at a step of its own that depends on the row alone, MMA_TURN steps further every MMA_ROWS
+   rows, and wrap: begun at the same step everywhere, the workgroups of a launch read equal offsets of
+   such rows at the same time, which lie on few memory channels (us a pass at 16 tokens, bf16: 128256 x
+   8192 408 -> 323, eight of 8192 x 8192 217 -> 167, 50000 x 16384 363 -> 294; rows of other lengths lose
+   up to 1.3 % by it: 8192 x 28672 286.8 -> 290.6, int8 8192 x 28672 462 -> 467). */
+constexpr int MMA_SPLIT = 4, MMA_TURN = 5, MMA_TURN_BYTES = 16 << 10;
 template <int FMT, int NT>
 constexpr int mma_ring_slots() { return 2 * MmaStep<FMT>::SLABS + (FMT == FMT_Q4 ? NT : 0); }
 
@@ -208,7 +213,7 @@ __device__ __forceinline__ void wait_vm() {
    NT KiB per wave), in wave order, each wave storing some of the tiles.  A wave alone (KS = 1, in
    tables of several formats) sums 16-bit and int8 rows in the same MMA_SPLIT parts and joins them in the
    same order, so that a matrix's outputs do not depend on what else its table holds. */
-template <int FMT, int NT, bool WHOLE, bool SHORT, int KS>
+template <int FMT, int NT, bool WHOLE, bool SHORT, int KS, bool TURN>
 __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1, int32_t token0, int ntok, int lane,
                                          int wave, u32x4* __restrict__ xlds, u32x4* __restrict__ joins) {
     static_assert(KS == 1 || FMT != FMT_Q4, "q4 scales come in blocks of four steps from the first on");
@@ -221,8 +226,8 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
     const int64_t kelem = FMT == FMT_Q4 ? nc * 32 : FMT == FMT_I8 ? nc * 16 : nc * 8;
     const int32_t steps = (int32_t)((crb + SB - 1) / SB);       /* at most 2^19 (rows up to 32 MiB) */
     const int64_t ngroups = (r1 - r0 + 16 * NT - 1) / (16 * NT);
-    const int32_t ks = KS == 1 ? 0 : (int32_t)((int64_t)steps * wave / KS);          /* this wave's steps */
-    const int32_t ke = KS == 1 ? steps : (int32_t)((int64_t)steps * (wave + 1) / KS);
+    const int32_t ks = KS == 1 ? 0 : steps * wave / KS;          /* this wave's steps */
+    const int32_t ke = KS == 1 ? steps : steps * (wave + 1) / KS;
     const int64_t n = ngroups * (ke - ks);                       /* units */
     const rsrc_t rx = buffer_of(uniform_ptr(static_cast<const char*>(d.x) + (int64_t)token0 * d.x_stride));
     const int64_t srow = FMT == FMT_Q4 ? nc * 2 : 2;             /* scale bytes per row */
@@ -233,14 +238,29 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
     f4_t sum[PARTS ? NT : 1];                                    /* the parts before the current one */
 #pragma unroll
     for (int t = 0; t < (PARTS ? NT : 1); ++t) sum[t] = f4_t{0.f, 0.f, 0.f, 0.f};
-    auto part_end = [&](int32_t k) {                             /* of the part that holds step k (steps: at most 2^19) */
-        int32_t p = 1;
-        while (p < MMA_SPLIT && steps * p / MMA_SPLIT <= k) ++p;
-        return steps * p / MMA_SPLIT;
+    /* A part (of a wave alone; else the wave's steps): steps [from, to), with TURN begun at step `first`. */
+    struct Part {
+        int32_t from, to, first;
     };
-    int32_t pend = PARTS ? part_end(0) : 0;
+    auto part_of = [&](int32_t k, int64_t g) {                   /* the part that holds step k of the group at r0 + 16 NT g */
+        Part p{ks, ke, 0};
+        if constexpr (PARTS) {
+            int32_t q = 1;
+            while (q < MMA_SPLIT && steps * q / MMA_SPLIT <= k) ++q;
+            p.from = steps * (q - 1) / MMA_SPLIT, p.to = steps * q / MMA_SPLIT;
+        }
+        if constexpr (TURN)
+            p.first = p.from + (int32_t)((uint32_t)((r0 + 16 * NT * g) / MMA_ROWS) * MMA_TURN % (uint32_t)(p.to - p.from));
+        return p;
+    };
+    auto turned = [&](const Part& p, int32_t k) {                /* what is taken as the part's step k */
+        if constexpr (!TURN) return k;
+        const int32_t t = k - p.from + p.first;
+        return t < p.to ? t : t - (p.to - p.from);
+    };
     int64_t gl = 0, gc = 0;                                      /* group of the next unit to load, multiply */
     int32_t kl = ks, kc = ks;                                    /* and its step                             */
+    Part pl{}, pc{};                                             /* the parts they lie in                    */
     int lbuf = 0, mbuf = 0;                                      /* LDS ring half of the next load, multiply */
     rsrc_t rw = buffer_of(d.w), rs = buffer_of(d.w);             /* this group's row r0 of codes, scales */
     uint32_t vr[NT], vs[NT];                                     /* lane offsets: row of each tile */
@@ -303,8 +323,9 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
                 vsb[j] = (uint32_t)((std::min<int64_t>(i0 + 16 * j + (lane >> 2), r1 - 1) - i0) * srow);
         }
         /* the last step ends at the row's end; offsets stay below 2^31 (the caller's limits) */
-        const uint32_t kb = SHORT ? 0 : (uint32_t)std::min<int64_t>((int64_t)kl * SB, crb - SB);
-        const uint32_t xo = SHORT ? 0 : (uint32_t)(std::min<int64_t>((int64_t)kl * SK, kelem - SK) * 2);
+        const int32_t kt = turned(pl, kl);
+        const uint32_t kb = SHORT ? 0 : (uint32_t)std::min<int64_t>((int64_t)kt * SB, crb - SB);
+        const uint32_t xo = SHORT ? 0 : (uint32_t)(std::min<int64_t>((int64_t)kt * SK, kelem - SK) * 2);
         const uint32_t b0 = SHORT ? 0 : (uint32_t)std::min<int64_t>((int64_t)kl * 8, nc - 8);   /* q4: first block */
         if (S_LDS && kl % MMA_SCALE_STEPS == 0) {              /* a new block of scales, first of all */
             wait_lds_idle();                                     /* the old block's reads are done */
@@ -347,6 +368,7 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
             }
         }
         if (++kl == ke) { kl = ks; ++gl; }
+        if (TURN && (kl == ks || kl == pl.to)) pl = part_of(kl, gl);
     };
     /* Vector memory operations each load() issues after its loads into LDS (weights, scales; the
        int8 row scales, loaded on a group's last step only, are left out: a wait that counts fewer
@@ -389,7 +411,8 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
         const int32_t k1 = kc + 1 == ke ? ks : kc + 1;           /* the next unit's step, and the one after */
         const int32_t k2 = k1 + 1 == ke ? ks : k1 + 1;
         /* the step's first weight, and the first one it has not already covered */
-        const int64_t e0 = SHORT ? 0 : std::min<int64_t>((int64_t)kc * SK, kelem - SK), e1 = SHORT ? 0 : (int64_t)kc * SK;
+        const int32_t kt = turned(pc, kc);
+        const int64_t e0 = SHORT ? 0 : std::min<int64_t>((int64_t)kt * SK, kelem - SK), e1 = SHORT ? 0 : (int64_t)kt * SK;
 #pragma unroll
         for (int t = 0; t < NT; ++t) lines_to_slabs(u.w[t][0], u.w[t][1]);
         {
@@ -498,13 +521,12 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
             }
         }
         if constexpr (PARTS) {
-            if (kc + 1 == pend) {
+            if (kc + 1 == pc.to) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     sum[t] += acc[t];
                     acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
                 }
-                pend = part_end(kc + 1 == ke ? 0 : kc + 1);
             }
         }
         if (kc + 1 == ke) {                                      /* end of a group: store, reset */
@@ -523,11 +545,14 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
             }
         }
         if (++kc == ke) { kc = ks; ++gc; }
+        if ((PARTS || TURN) && (kc == ks || kc == pc.to)) pc = part_of(kc, gc);
     };
     if (KS > 1 && n == 0) {                                      /* fewer steps than waves: none for this one */
         for (int64_t g = 0; g < ngroups; ++g) join(r0 + g * 16 * NT);
         return;
     }
+    if (KS == 1 && n == 0) return;
+    if constexpr (PARTS || TURN) pl = pc = part_of(ks, 0);
     Unit buf[2];
     const std::true_type next_loaded;
     const std::false_type last;
@@ -582,28 +607,32 @@ __device__ __forceinline__ void stream_range_mma(const DevMat* __restrict__ tab,
         }
         if (rr.r0 >= rr.r1) continue;
         const bool short_rows = d.nc * 16 < 128;                 /* under one step */
-#define WSR_ROWS(F, W, SH) rows_mma<F, NT, W, SH, KS>(d, rr.r0, rr.r1, token0, ntok, lane, wave, xlds, joins)
+#define WSR_ROWS(F, W, SH, TU) rows_mma<F, NT, W, SH, KS, TU>(d, rr.r0, rr.r1, token0, ntok, lane, wave, xlds, joins)
         const bool whole = d.nc % 8 == 0;                        /* 128-byte steps: 8 chunks or blocks */
+        const bool turn = d.nc * 16 % MMA_TURN_BYTES == 0;
         if constexpr (FMT == FMT_Q4_WHOLE) {                     /* the launcher checked every matrix */
-            WSR_ROWS(FMT_Q4, true, false);
+            WSR_ROWS(FMT_Q4, true, false, false);
         } else if ((F == 0 || F == FMT_F16) && fmt == FMT_F16) {
-            if (short_rows) WSR_ROWS(FMT_F16, false, true);
-            else if (whole) WSR_ROWS(FMT_F16, true, false);
-            else WSR_ROWS(FMT_F16, false, false);
+            if (short_rows) WSR_ROWS(FMT_F16, false, true, false);
+            else if (turn) WSR_ROWS(FMT_F16, true, false, true);
+            else if (whole) WSR_ROWS(FMT_F16, true, false, false);
+            else WSR_ROWS(FMT_F16, false, false, false);
         } else if ((F == 0 || F == FMT_BF16) && fmt == FMT_BF16) {
-            if (short_rows) WSR_ROWS(FMT_BF16, false, true);
-            else if (whole) WSR_ROWS(FMT_BF16, true, false);
-            else WSR_ROWS(FMT_BF16, false, false);
+            if (short_rows) WSR_ROWS(FMT_BF16, false, true, false);
+            else if (turn) WSR_ROWS(FMT_BF16, true, false, true);
+            else if (whole) WSR_ROWS(FMT_BF16, true, false, false);
+            else WSR_ROWS(FMT_BF16, false, false, false);
         } else if ((F == 0 || F == FMT_Q4) && fmt == FMT_Q4) {
             if constexpr (KS == 1) {                             /* (a launch that holds q4 does not split) */
-                if (short_rows) WSR_ROWS(FMT_Q4, false, true);
-                else if (whole && (reinterpret_cast<uintptr_t>(d.s) & 15) == 0) WSR_ROWS(FMT_Q4, true, false);
-                else WSR_ROWS(FMT_Q4, false, false);
+                if (short_rows) WSR_ROWS(FMT_Q4, false, true, false);
+                else if (whole && (reinterpret_cast<uintptr_t>(d.s) & 15) == 0) WSR_ROWS(FMT_Q4, true, false, false);
+                else WSR_ROWS(FMT_Q4, false, false, false);
             }
         } else if ((F == 0 || F == FMT_I8) && fmt == FMT_I8) {
-            if (short_rows) WSR_ROWS(FMT_I8, false, true);
-            else if (whole) WSR_ROWS(FMT_I8, true, false);
-            else WSR_ROWS(FMT_I8, false, false);
+            if (short_rows) WSR_ROWS(FMT_I8, false, true, false);
+            else if (turn) WSR_ROWS(FMT_I8, true, false, true);
+            else if (whole) WSR_ROWS(FMT_I8, true, false, false);
+            else WSR_ROWS(FMT_I8, false, false, false);
         }
 #undef WSR_ROWS
     }

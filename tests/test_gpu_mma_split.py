@@ -1,6 +1,7 @@
 """The matrix-core sweep whose workgroups split every row's steps over four waves (16-bit, int8): rows of
-fewer steps than waves (some waves have none), of uneven shares and with a ragged last step, over
-several row groups with a ragged last one, several matrices in one call and the outputs' bounds."""
+fewer steps than waves (some waves have none), of uneven shares, with a ragged last step and of 16 KiB
+(128 steps: each row group begins at a step of its own), over several row groups with a ragged last
+one, several matrices in one call and the outputs' bounds."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +21,7 @@ STEP = {wl.F16: 64, wl.BF16: 64, wl.I8: 128}      # weights of a 128-byte step
 
 
 @pytest.mark.parametrize("fmt", [wl.F16, wl.BF16, wl.I8])
-@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 9])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 9, 128, 256])
 @pytest.mark.parametrize("ragged", [0, 16], ids=["whole", "ragged"])
 def test_split_steps(fmt, steps, ragged):
     M, T, K = 150, 5, steps * STEP[fmt] + ragged
@@ -44,7 +45,7 @@ def mma_table(entries, T):
     return [f32_bits(y.cpu().numpy()) for y in ys]
 
 
-@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 9, 30])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 9, 30, 128])
 @pytest.mark.parametrize("ragged", [0, 16, -48], ids=["whole", "longer", "shorter"])
 def test_outputs_do_not_depend_on_the_rest_of_the_table(steps, ragged):
     """A matrix's outputs are the same bits alone, and in a table that holds other formats too, where one
@@ -57,3 +58,22 @@ def test_outputs_do_not_depend_on_the_rest_of_the_table(steps, ragged):
         entries.append((fmt, M, K, dv.to_device(W), None if S is None else dv.to_device(S), dv.to_device(X)))
     for e, got in zip(entries, mma_table(entries, T)):
         assert np.array_equal(got, mma_table([e], T)[0]), (e[0], e[2])
+
+
+@pytest.mark.parametrize("fmt", [wl.BF16, wl.I8])
+def test_rows_of_16_kib_do_not_depend_on_their_workgroup(fmt):
+    """Row groups in the spans' main part and in the tail (581 groups of 64 rows leave one), and the same rows
+    as matrices of their own: the same bits, since the step a row begins at depends on the row alone (and
+    repeats every 32 groups)."""
+    T, K, M = 5, STEP[fmt] * 128, 2048 * 18 + 300
+    g = torch.Generator(device="cuda").manual_seed(11)
+    W = torch.randn((M, K), device="cuda", generator=g)
+    W = (W * 40).to(torch.int8) if fmt == wl.I8 else W.to(torch.bfloat16)
+    S = torch.rand(M, device="cuda", generator=g).to(torch.float16) if fmt == wl.I8 else None
+    X = torch.randn((T, K), device="cuda", generator=g).to(torch.float16 if fmt == wl.I8 else torch.bfloat16)
+    whole = mma_table([(fmt, M, K, W, S, X)], T)[0]
+    for r0, n in ((0, 150), (2048 * 9, 64), (2048 * 17, M - 2048 * 17), (2048 * 18, 300)):
+        part = mma_table([(fmt, n, K, W[r0:r0 + n], None if S is None else S[r0:r0 + n], X)], T)[0]
+        assert np.array_equal(part, whole[:, r0:r0 + n]), r0
+    del W, X
+    torch.cuda.empty_cache()
