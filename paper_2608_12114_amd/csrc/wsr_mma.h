@@ -551,7 +551,6 @@ __device__ __forceinline__ void rows_mma(const DevMat& d, int64_t r0, int64_t r1
         for (int64_t g = 0; g < ngroups; ++g) join(r0 + g * 16 * NT);
         return;
     }
-    if (KS == 1 && n == 0) return;
     if constexpr (PARTS || TURN) pl = pc = part_of(ks, 0);
     Unit buf[2];
     const std::true_type next_loaded;
@@ -606,6 +605,14 @@ __device__ __forceinline__ void stream_range_mma(const DevMat* __restrict__ tab,
             rr.r1 = rr.r1 > f ? rr.r1 : f;
         }
         if (rr.r0 >= rr.r1) continue;
+        if (d.nc == 0) {                                         /* empty rows: empty sums */
+            for (int64_t r = rr.r0 + wave * WAVE + lane; r < rr.r1; r += KS * WAVE) {
+                const float v = fmt == FMT_I8 ? 0.f * f16_bits_to_f32(as_global<g_u16*>(d.s)[r]) : 0.f;
+                for (int t = 0; t < ntok; ++t)
+                    as_global<g_f32*>(reinterpret_cast<char*>(d.y) + (int64_t)(token0 + t) * d.y_stride)[r] = v;
+            }
+            continue;
+        }
         const bool short_rows = d.nc * 16 < 128;                 /* under one step */
 #define WSR_ROWS(F, W, SH, TU) rows_mma<F, NT, W, SH, KS, TU>(d, rr.r0, rr.r1, token0, ntok, lane, wave, xlds, joins)
         const bool whole = d.nc % 8 == 0;                        /* 128-byte steps: 8 chunks or blocks */

@@ -77,3 +77,12 @@ def test_rows_of_16_kib_do_not_depend_on_their_workgroup(fmt):
         assert np.array_equal(part, whole[:, r0:r0 + n]), r0
     del W, X
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("fmts", [(wl.F16,), (wl.BF16,), (wl.I8,), (wl.Q4,), (wl.Q4, wl.F16, wl.I8)], ids=str)
+def test_empty_rows_give_empty_sums(fmts):
+    """K = 0: every output is 0, in tables of one format and of several."""
+    any16 = torch.ones(4096, dtype=torch.uint8, device="cuda")
+    entries = [(fmt, M, 0, any16, any16 if fmt in (wl.Q4, wl.I8) else None, any16) for fmt in fmts for M in (1, 64, 150)]
+    for y in mma_table(entries, 3):
+        assert not y.any()
