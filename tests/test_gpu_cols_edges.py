@@ -1,6 +1,6 @@
 """Multi-column GEMVs at the edges of their kernels: columns between the powers of two the quads hold,
 rows around a round, chunks around a quarter, a step and the steps LDS holds, both kernels, unaligned
-strides, non-finite and subnormal 16-bit values.  Every column must equal the single-column GEMV bit
+strides, rows of 256 MiB, non-finite and subnormal values.  Every column must equal the single-column GEMV bit
 for bit (the contract of include/wsr.h), which the oracle tests hold to 2e-3."""
 import numpy as np
 import pytest
@@ -62,10 +62,33 @@ def test_short_streams(fmt, T, chunks):
                                          (wl.I8, 4, 9), (wl.I8, 8, 4), (wl.I8, 8, 5), (wl.BF16, 8, 10), (wl.BF16, 8, 11),
                                          (wl.F16, 16, 5), (wl.F16, 16, 6), (wl.F16, 16, 1)])
 def test_long_streams(fmt, T, steps):
-    """Enough rounds for the kernel that shares activations through LDS: rows that stay there whole and
-    rows one step too long, with a last step of 64, 1 and 33 chunks, and a ragged last round."""
+    """Enough rounds of 32 rows (over 384; over 512 for int8 with four columns) for the kernel that shares
+    activations through LDS: rows that stay there whole and rows one step too long, with a last step
+    of 64, 1 and 33 chunks, and a ragged last round."""
+    rounds = 520 if fmt == wl.I8 and T <= 4 else 400
     for last in (64, 1, 33):
-        compare(fmt, 32 * 400 + 5, STEP[fmt] * (steps - 1) + UNIT[fmt] * last, T)
+        compare(fmt, 32 * rounds + 5, STEP[fmt] * (steps - 1) + UNIT[fmt] * last, T)
+
+
+@pytest.mark.parametrize("T", [2, 4, 8])
+def test_mixed_table_of_long_and_short_rows(T):
+    """A table of several formats, 1,200 rounds for at most 512 workgroups, so that each goes through two or
+    three matrices: rows longer than LDS holds (a ring of two steps) and short ones (kept whole) in
+    turn, of one format and of another, all with the same activations."""
+    LONG, SHORT, M = 32 * 321, 544, 33                       # LONG: 21, 6 and 11 steps of 16-bit, q4, int8 rows
+    X = dv.to_device(synth.normal16((T, LONG), wl.X_SIGMA, wl.F16, seed=12, stream=707))
+    made = {(f, K): matrix(f, M, K, seed=K) for f in (wl.F16, wl.Q4, wl.I8) for K in (LONG, SHORT)}
+    order = [(wl.F16, LONG), (wl.F16, SHORT), (wl.Q4, SHORT), (wl.Q4, LONG), (wl.I8, SHORT), (wl.F16, SHORT), (wl.I8, LONG),
+             (wl.I8, SHORT), (wl.Q4, SHORT), (wl.F16, LONG), (wl.I8, LONG), (wl.Q4, LONG)] * 50
+    y = torch.full((2, len(order), T, M + 1), float("nan"), dtype=torch.float32, device="cuda")
+    for i, batch in enumerate((1, T)):
+        mats = wsr.make_mats([dict(fmt=FMT[f], M=M, K=K, w=made[f, K][0], scales=made[f, K][1], x=X, x_tok_stride=2 * LONG,
+                                   y=y[i, m], y_tok_stride=4 * (M + 1)) for m, (f, K) in enumerate(order)])
+        ws = zeros_u8(wsr.wsr_sweep_workspace_bytes(mats))
+        wsr.wsr_decode_sweep_batched(mats, T, batch, ws, ws.numel(), stream())
+    torch.cuda.synchronize()
+    assert torch.isnan(y[..., M]).all() and not torch.isnan(y[..., :M]).any()
+    assert torch.equal(y[0, ..., :M].contiguous().view(torch.int32), y[1, ..., :M].contiguous().view(torch.int32))
 
 
 @pytest.mark.parametrize("fmt,T,M", [(wl.F16, 2, 16387), (wl.BF16, 2, 16383), (wl.I8, 2, 32 * 512 + 3), (wl.I8, 2, 32 * 511)])
@@ -132,3 +155,113 @@ def test_values_at_the_ends_of_16_bit_formats(fmt, T, M):
     nan = np.isnan(one)
     assert np.array_equal(nan, np.isnan(many)) and nan.any() and not nan.all()
     assert np.array_equal(f32_bits(one)[~nan], f32_bits(many)[~nan])
+
+
+def same_bits(fmt, W, S, Xh, M, K, T):
+    X = dv.to_device(Xh)
+    one, many = (batched(fmt, W, S, X, M, K, T, b) for b in (1, T))
+    nan = np.isnan(one)
+    assert np.array_equal(nan, np.isnan(many))
+    assert np.array_equal(f32_bits(one)[~nan], f32_bits(many)[~nan])
+    return one
+
+
+@pytest.mark.parametrize("fmt", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("T,M", [(2, 40), (4, 40), (8, 40), (16, 40), (8, 32 * 400), (16, 32 * 400)])
+def test_products_of_subnormal_values_alone(fmt, T, M):
+    """Rows whose only weights are subnormal, against ordinary activations, the largest finite ones and
+    subnormal ones: the outputs are those products and their sums alone, so that a matrix instruction
+    that took a subnormal operand, product or sum for zero, or rounded it another way, would show."""
+    K = 264
+    rng = np.random.default_rng(17)
+    sub = np.concatenate([np.arange(1, 128), 0x8000 + np.arange(1, 128)]).astype(np.uint16)   # subnormal in both formats
+    Wh = np.zeros((M, K), np.uint16)
+    for row in range(M):
+        n = (1, 2, 5, K)[row % 4]
+        Wh[row, rng.choice(K, n, replace=False)] = rng.choice(sub, n)
+    big = 0x7BFF if fmt == wl.F16 else 0x7F7F
+    Xh = synth.normal16((T, K), wl.X_SIGMA, fmt, seed=18, stream=708)
+    Xh[1] = rng.choice(np.array([big, big | 0x8000, big - 1, 0x3C00, 0x3F80], np.uint16), K)
+    if T > 2:
+        Xh[2] = rng.choice(sub, K)
+        Xh[3] = rng.choice(np.array([0x0080, 0x8080, 0x0400, 0x8400, 0x1000], np.uint16), K)   # the smallest normal ones
+    one = same_bits(fmt, dv.to_device(Wh), None, Xh, M, K, T)
+    assert np.isfinite(one).all() and one[0].any() and one[1].any()
+
+
+@pytest.mark.parametrize("fmt", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("T,M", [(4, 40), (16, 32 * 400)])
+def test_small_results(fmt, T, M):
+    """Small weights against small activations: products and sums down to the smallest results of the
+    format's products, fp32 subnormals among them for bf16."""
+    K = 264
+    rng = np.random.default_rng(19)
+    lo, hi = (0x0001, 0x1000) if fmt == wl.F16 else (0x0001, 0x2800)
+    Wh = (rng.integers(lo, hi, (M, K)) | rng.choice([0, 0x8000], (M, K))).astype(np.uint16)
+    Xh = (rng.integers(lo, hi, (T, K)) | rng.choice([0, 0x8000], (T, K))).astype(np.uint16)
+    same_bits(fmt, dv.to_device(Wh), None, Xh, M, K, T)
+
+
+@pytest.mark.parametrize("fmt", [wl.Q4, wl.I8])
+@pytest.mark.parametrize("T,M", [(2, 40), (4, 40), (8, 40), (4, 32 * 520), (8, 32 * 400)])
+def test_activations_that_are_not_finite(fmt, T, M):
+    """An infinity or NaN among the activations of one token makes that token's outputs NaN (an infinity meets
+    the decoders' offset terms too), single and in a column, and touches no other token; activations at
+    the ends of fp16 keep their bits."""
+    K = 1120
+    W, S = matrix(fmt, M, K, seed=23)
+    Xh = synth.normal16((T, K), wl.X_SIGMA, wl.F16, seed=23, stream=709)
+    Xh[0, [3, 700]] = 0x7BFF, 0x0001
+    Xh[1, 1119] = 0x7C00
+    if T > 2:
+        Xh[2, 64] = 0x7E00
+        Xh[3, [0, 555]] = 0xFC00, 0x7C00
+    one = same_bits(fmt, W, S, Xh, M, K, T)
+    assert np.isnan(one[1:4]).all() and np.isfinite(one[0]).all() and np.isfinite(one[4:]).all()
+
+
+@pytest.mark.parametrize("fmt,M,K", [(wl.F16, 3, 1 << 27), (wl.BF16, 2, (1 << 27) - 8), (wl.Q4, 5, (1 << 29) + 32), (wl.I8, 5, 1 << 28),
+                                     (wl.I8, 2, (1 << 28) - 16)])
+def test_rows_of_256_mib(fmt, M, K):
+    """Rows at the limit of the kernels' 32-bit offsets (2^24 chunks) and one chunk below: columns equal the
+    single column bit for bit, through the GEMV and the sweep, alone and beside a short matrix, and the
+    products of the few activations that are not zero, at both ends of the row among them."""
+    T, n = 2, 200
+    nb, sb = {wl.Q4: K // 2, wl.I8: K}.get(fmt, 2 * K), {wl.Q4: K // 16, wl.I8: 2}.get(fmt, 0)
+    g = torch.Generator(device="cuda").manual_seed(29)
+    w = torch.randint(0, 60, (M * nb,), dtype=torch.uint8, device="cuda", generator=g)          # 16-bit: finite, up to 1.2
+    s = torch.full((max(8, M * sb // 2),), 0x2C00, dtype=torch.int16, device="cuda")            # fp16 1 / 16
+    at = torch.cat([torch.tensor([0, 1, K // 2, K - 2, K - 1], device="cuda"), torch.randint(0, K, (n,), device="cuda", generator=g)])
+    x = torch.zeros((T, K), dtype=torch.bfloat16 if fmt == wl.BF16 else torch.float16, device="cuda")
+    x[:, at] = torch.randn((T, n + 5), device="cuda", generator=g).to(x.dtype)
+    pos = at.unique()
+    if fmt in (wl.F16, wl.BF16):
+        wd = w.view(x.dtype).view(M, K)[:, pos].double()
+    elif fmt == wl.I8:
+        wd = w.view(torch.int8).view(M, K)[:, pos].double() / 16
+    else:
+        q = (w.view(M, K // 2)[:, pos // 2] >> (4 * (pos % 2)).to(torch.uint8)) & 15
+        wd = ((q ^ 8).double() - 8) / 16
+    want = x[:, pos].double() @ wd.t()
+    y = torch.full((4, T, M), float("nan"), dtype=torch.float32, device="cuda")
+    small = torch.zeros((2, T, 4), dtype=torch.float32, device="cuda")
+    rec = dict(fmt=FMT[fmt], M=M, K=K, w=w, scales=s if sb else None, x=x, x_tok_stride=2 * K, y_tok_stride=4 * M)
+    short = dict(rec, M=4, K=64, x_tok_stride=2 * K, y_tok_stride=16)
+    for i, (batch, records) in enumerate(((1, [dict(rec, y=y[0])]), (T, [dict(rec, y=y[1])]),
+                                          (T, [dict(short, y=small[0]), dict(rec, y=y[2]), dict(short, y=small[1])]))):
+        mats = wsr.make_mats(records)
+        ws = zeros_u8(wsr.wsr_sweep_workspace_bytes(mats))
+        wsr.wsr_decode_sweep_batched(mats, T, batch, ws, ws.numel(), stream())
+    cols = y[3]
+    if fmt in (wl.F16, wl.BF16):
+        wsr.wsr_gemv_f16_cols(w, x, 2 * K, cols, 4 * M, M, K, T, FMT[fmt], stream())
+    else:
+        (wsr.wsr_gemv_q4_cols if fmt == wl.Q4 else wsr.wsr_gemv_i8_cols)(w, s, x, 2 * K, cols, 4 * M, M, K, T, stream())
+    torch.cuda.synchronize()
+    for i in range(1, 4):
+        assert torch.equal(y[i].view(torch.int32), y[0].view(torch.int32)), i
+    # sums of at most 205 exact products in fp32, and of the decoders' offset terms (q4 8, int8 128 times an activation)
+    bound = 205 * 2.0 ** -24 * (x[:, pos].double().abs() @ (wd.abs() + {wl.Q4: 0.5, wl.I8: 8.0}.get(fmt, 0.0)).t())
+    assert ((y[0].double() - want).abs() <= bound).all()
+    del w, x
+    torch.cuda.empty_cache()
