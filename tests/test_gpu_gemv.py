@@ -198,3 +198,28 @@ def test_more_rows_than_one_launch_holds(fmt, M, K):
         assert torch.equal(part.view(torch.int32), y[0, at:at + n].view(torch.int32)), at
     del w, s, y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("fmt,M,K", [(wsr.WSR_BF16, 1024, 4096), (wsr.WSR_BF16, 1025, 4096), (wsr.WSR_F16, 64, 4104),
+                                     (wsr.WSR_F16, 2048, 512), (wsr.WSR_F16, 2049, 512), (wsr.WSR_Q4, 1820, 2048),
+                                     (wsr.WSR_Q4, 1821, 2048), (wsr.WSR_Q4, 455, 4096), (wsr.WSR_Q4, 456, 4096),
+                                     (wsr.WSR_Q4, 3, 4128), (wsr.WSR_I8, 2044, 1024), (wsr.WSR_I8, 2045, 1024), (wsr.WSR_I8, 1, 2064)])
+def test_both_argument_forms(fmt, M, K):
+    """Both sides of the rule by which a GEMV's matrix goes as one structure or as single arguments, against
+    the sweep over more matrices than it takes as row groups."""
+    nb = {wsr.WSR_Q4: K // 2, wsr.WSR_I8: K}.get(fmt, 2 * K)
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    w = torch.randint(0, 60, (M * nb,), dtype=torch.uint8, device="cuda", generator=g)
+    s = torch.randint(0x2800, 0x2C00, (M * max(1, K // 32),), dtype=torch.int16, device="cuda", generator=g)
+    x = torch.randn(K, device="cuda", generator=g).to(torch.bfloat16 if fmt == wsr.WSR_BF16 else torch.float16)
+    y = torch.full((10, M + 1), float("nan"), dtype=torch.float32, device="cuda")
+    if fmt in (wsr.WSR_F16, wsr.WSR_BF16):
+        wsr.wsr_gemv_f16(w, x, y[0], M, K, fmt, stream())
+    else:
+        (wsr.wsr_gemv_q4 if fmt == wsr.WSR_Q4 else wsr.wsr_gemv_i8)(w, s, x, y[0], M, K, stream())
+    mats = wsr.make_mats([dict(fmt=fmt, M=M, K=K, w=w, scales=s, x=x, y=y[i]) for i in range(1, 10)])
+    ws = torch.zeros(wsr.wsr_sweep_workspace_bytes(mats), dtype=torch.uint8, device="cuda")
+    wsr.wsr_decode_sweep(mats, 1, ws, ws.numel(), stream())
+    torch.cuda.synchronize()
+    assert torch.isnan(y[:, M]).all() and not torch.isnan(y[:, :M]).any()
+    assert torch.equal(y[:, :M].contiguous().view(torch.int32), y[0:1, :M].expand(10, M).contiguous().view(torch.int32))

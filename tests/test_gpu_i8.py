@@ -159,10 +159,11 @@ def test_sweep_with_i8_batched_equals_sequential(model_i8, batch):
 
 @pytest.mark.parametrize("M,K", [(1000, 2064), (1003, 4096), (517, 1024), (75, 7168)])
 def test_sweep_i8_only_equals_gemv(M, K):
-    """A table of int8 matrices only (the uniform int8 sweep kernel) reproduces wsr_gemv_i8 bit
-    for bit, matrix by matrix: rows of whole 64-chunk steps (K a multiple of 1024) take the
-    pipelined row loop, across row groups and with ragged row counts, the others the plain one."""
-    mats = wl.protocol_matrices(n=5, M=M, K=K)
+    """A table of int8 matrices only reproduces wsr_gemv_i8 bit for bit, matrix by matrix: more matrices than
+    the launch of row groups takes (8), so that they go over spans in the pipelined row loop, across row
+    groups and with ragged row counts, rows of whole 64-chunk steps (K a multiple of 1024) and others.
+    Spans hold 32 KiB or more: several groups of 8 rows at K of 2,064 and less."""
+    mats = wl.protocol_matrices(n=9, M=M, K=K)
     inp = dv.SweepInputs(mats, [wl.I8] * len(mats), tokens=2)
     ys = run(inp, 2)
     for i, m in enumerate(mats):

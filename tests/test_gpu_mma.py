@@ -84,12 +84,11 @@ def test_mma_matrix_parity_and_bounds(fmt, T):
         assert rel_l2(y[t, :M], want) <= TOL, (fmt, t)
 
 
-# groups of 128 rows (eight tiles: 16-bit at any token count, q4 from 8 tokens, int8 from 12) over
-# several whole groups and a ragged last one, against four tiles where the token count picks them
-GROUPS128 = [(wl.BF16, 300, 1000), (wl.F16, 129, 512), (wl.Q4, 300, 2048), (wl.Q4, 260, 2080), (wl.I8, 300, 1024)]
+# several whole groups of 64 rows and a ragged last one, at two to sixteen tokens
+GROUPS = [(wl.BF16, 300, 1000), (wl.F16, 129, 512), (wl.Q4, 300, 2048), (wl.Q4, 260, 2080), (wl.I8, 300, 1024)]
 
 
-@pytest.mark.parametrize("fmt,M,K", GROUPS128, ids=lambda v: str(v))
+@pytest.mark.parametrize("fmt,M,K", GROUPS, ids=lambda v: str(v))
 @pytest.mark.parametrize("T", [2, 8, 12, 16])
 def test_mma_row_groups_parity_and_bounds(fmt, M, K, T):
     W, S = host_matrix(fmt, M, K, seed=13)

@@ -85,18 +85,27 @@ def test_last_block_of_a_q4_row_with_an_infinite_scale():
     assert np.array_equal(f32_bits(got[0]), f32_bits(got[1]))
 
 
-# 16-bit streams of over 8 GiB run over spans: table in the arguments (136 matrices) and in the
-# workspace (300), the same 64 MiB of weights in every record
+# 16-bit streams: over spans with the table in the arguments (136 matrices of 67 MB) and in the workspace
+# (300, 1,023), and from 64 GiB on (1,024) over claimed tiles, whose counters each token leaves at zero for
+# the next one.  Record i begins i rows into one buffer of weights and 8 i elements into one of
+# activations, so that no two give the same outputs.
 @pytest.mark.parametrize("fmt", [wl.F16, wl.BF16])
-@pytest.mark.parametrize("n", [136, 300])
+@pytest.mark.parametrize("n", [136, 300, 1023, 1024, 1040])
 def test_long_16bit_stream(fmt, n):
-    M, K = 4099, 8192
-    (W, _), xh = matrix(fmt, M, K, seed=n)
-    w, x = dv.to_device(W), dv.to_device(xh)
-    one = torch.full((M,), float("nan"), dtype=torch.float32, device="cuda")
-    wsr.wsr_gemv_f16(w, x, one, M, K, FMT[fmt], stream())
-    ys = torch.full((n, M + 1), float("nan"), dtype=torch.float32, device="cuda")
-    sweep([spec(fmt, M, K, w, None, x, ys[i]) for i in range(n)])
+    M, K, T = 4099, 8192, 2
+    assert (n >= 1024) == (n * M * K * 2 >= 64 << 30)
+    w = dv.to_device(synth.normal16((M + n, K), wl.W_SIGMA, fmt, seed=n, stream=801))
+    x = dv.to_device(synth.normal16((T, K + 8 * n), wl.X_SIGMA, fmt, seed=n, stream=803))
+    ys = torch.full((n, T, M + 1), float("nan"), dtype=torch.float32, device="cuda")
+    one = torch.full((n, T, M), float("nan"), dtype=torch.float32, device="cuda")
+    specs = [dict(fmt=FMT[fmt], M=M, K=K, w=w[i:], scales=None, x=x[0, 8 * i:], x_tok_stride=2 * (K + 8 * n), y=ys[i],
+                  y_tok_stride=4 * (M + 1)) for i in range(n)]
+    mats = wsr.make_mats(specs)
+    ws = zeros_u8(wsr.wsr_sweep_workspace_bytes(mats))
+    wsr.wsr_decode_sweep(mats, T, ws, ws.numel(), stream())
+    for i in range(n):
+        for t in range(T):
+            wsr.wsr_gemv_f16(w[i:], x[t, 8 * i:], one[i, t], M, K, FMT[fmt], stream())
     torch.cuda.synchronize()
-    assert torch.equal(ys[:, :M].view(torch.int32), one.view(torch.int32).expand(n, M))
-    assert torch.isnan(ys[:, M]).all()
+    assert torch.equal(ys[..., :M].contiguous().view(torch.int32), one.view(torch.int32))
+    assert torch.isnan(ys[..., M]).all() and not torch.equal(one[0], one[1])

@@ -48,9 +48,9 @@ def _check(inp, tokens, chained=False):
 
 
 def test_noalloc_two_calls_second_smaller():
-    """A mixed-format model (one launch per token), then a smaller bf16 model (claimed tiles, whose
-    counters live in the scratch) in the next call, then the first model again with dependency
-    boundaries (several launches per token)."""
+    """A mixed-format model (one launch per token over claimed tiles, whose counters and table live in the
+    scratch), then a smaller bf16 model (its table in the launch arguments) in the next call, then the
+    first model again with dependency boundaries (several launches per token)."""
     big = wl.decode_matrices(dv.small_model(layers=3, d=512, ffn=1536, vocab=3000))
     big_in = dv.SweepInputs(big, [(wl.Q4, wl.BF16, wl.I8, wl.F16)[m.layer] for m in big], tokens=3)
     small = wl.decode_matrices(dv.small_model(layers=1, d=256, ffn=512, vocab=700))
