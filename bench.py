@@ -8,7 +8,8 @@ fully HBM-resident; one step = one decode token = one persistent launch over eve
 The headline and q4 sweeps (and the protocol) also report the same tokens batched b per weight
 pass, on the vector ALUs (bit-identical outputs) and on the matrix cores (b <= 16, within rounding).
 
-Also measured in the same run and reported under "rows" (same JSON line):
+Also measured in the same run and summarised under "rows" of the same JSON line, which is kept short; the
+whole record is a line on stderr ("[bench] record {...}") and, with --record FILE, a file:
   probe        pure-read reference, 1 GiB fp32 -> fp64 sum, HBM-resident and host-mapped
   gemv_f16     4096 x 4096 fp16 GEMV, 32 distinct matrices visited per pass (1 GiB)
   llama8b_q4   decode sweep of the Llama-3-8B shape in 4-bit blocks (4.22 GB per token)
@@ -101,6 +102,7 @@ def parse():
     p.add_argument("--processes", type=int, default=0,
                    help="run the headline in this many child processes, one after another, and report "
                         "the median of their medians (a separate JSON line; no GPU use in this process)")
+    p.add_argument("--record", default="", help="also write the whole record, all rows with every figure, to this file")
     return p.parse_args()
 
 
@@ -983,6 +985,54 @@ def measured_ceiling(head_gbps, rows):
                     "bytes, so its ramp and drain weigh less and the fraction can exceed 1"}
 
 
+LINE_MAX = 1800     # characters of the result line: whoever keeps only the last 2,000 of stdout has it whole
+
+
+def row_summary(rows):
+    """The figures of each row that the result line carries."""
+    def at(r, *path):
+        for k in path:
+            r = r.get(k) if isinstance(r, dict) else None
+        return round(r, 3 if abs(r) < 10 else 1) if isinstance(r, (int, float)) else r
+
+    def tokens(r, key, b):
+        return next((round(e["tokens_per_s"], 1) for e in r.get(key) or [] if e["batch"] == b), None)
+
+    take = {
+        "probe": lambda r: {"GBps": at(r, "resident_GBps"), "mapped_GBps": at(r, "mapped_GBps")},
+        "gemv_f16": lambda r: {"us": at(r, "us_per_gemv"), "GBps": at(r, "GBps_per_dispatch"),
+                               "one_launch_GBps": at(r, "one_launch_32_matrices_GBps")},
+        "llama8b_q4": lambda r: {"GBps": at(r, "GBps"), "tok_s": at(r, "tokens_per_s"), "batch8_tok_s": tokens(r, "batched", 8),
+                                 "matrix_cores16_tok_s": tokens(r, "batched_matrix_cores", 16),
+                                 "traffic": at(r, "roofline", "traffic")},
+        "protocol": lambda r: {"one_launch_GBps": at(r, "one_launch_back_to_back", "GBps_at_median"),
+                               "dispatches_GBps": at(r, "dispatches_12", "GBps_at_median"),
+                               "batch8_tok_s": tokens(r, "batched", 8),
+                               "matrix_cores16_tok_s": tokens(r, "batched_matrix_cores", 16)},
+        "endpoints": lambda r: {k: at(r, "GBps", k) for k in r.get("GBps") or {}} | {"choice": at(r, "alg2", "choice")},
+        "ordering": lambda r: {k: at(v, "excess", "event", "median_ms") for k, v in (r.get("results") or {}).items()},
+        "size_sweep": lambda r: {"plateau_GBps": at(r, "crossovers", "resident_plateau_GBps"),
+                                 "smallest_us": at((r.get("points") or [{}])[0], "resident_us")},
+        "bus": lambda r: {"h2d_GBps": at(r, "h2d_GBps")},
+    }
+    return {k: take[k](r) for k, r in rows.items() if k in take}
+
+
+def short_line(record):
+    """The one line on stdout: the headline whole and a summary of the rest, at most LINE_MAX characters (the
+    whole record goes to stderr, and to a file with --record)."""
+    line = {k: v for k, v in record.items() if k not in ("cpu_baseline", "parity", "passes", "probe_ceiling", "rows")}
+    pick = {"cpu_baseline": ("value", "unit", "cores", "kind"), "parity": ("worst_rel_l2",), "passes": ("n", "median", "iqr"),
+            "probe_ceiling": ("GBps", "frac")}
+    for k, fields in pick.items():
+        if record.get(k):
+            line[k] = {f: record[k][f] for f in fields if f in record[k]}
+    line["rows"] = row_summary(record["rows"])
+    while len(json.dumps(line)) > LINE_MAX and line["rows"]:
+        line["rows"].popitem()
+    return json.dumps(line)
+
+
 def main():
     args = parse()
     world = int(os.environ.get("WORLD_SIZE", "1"))
@@ -1031,7 +1081,7 @@ def main():
     probe_ceiling = measured_ceiling(gbps, rows)
     dtype = {"llama70b_bf16": "bf16", "llama8b_q4": "q4+f16"}[args.workload]
     traffic, traffic_src = profiled_traffic(args.workload)
-    line = {
+    record = {
         "metric": "achieved GB/s (% of HBM peak) for decode-step GEMV sweep; tokens/s at batch 1",
         "value": round(gbps, 2), "unit": "GB/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(head["ms_per_token"], 4), "higher_is_better": True, "scaling": "weak",
@@ -1052,7 +1102,11 @@ def main():
         "rows": rows,
         "wall_s": round(time.time() - t_start, 1),
     }
-    print(json.dumps(line), flush=True)
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(record, f, indent=1)
+    log("record " + json.dumps(record))
+    print(short_line(record), flush=True)
 
 
 if __name__ == "__main__":

@@ -103,3 +103,38 @@ def test_measured_ceiling_second_denominator():
     assert rows["gemv_f16"]["frac_of_probe"] == 0.5
     assert "frac_of_probe" not in rows["probe"] and "frac_of_probe" not in rows["endpoints"]
     assert bench.measured_ceiling(7140.0, {"gemv_f16": {"roofline": {"achieved": 1.0}}}) is None
+
+
+def test_result_line_is_one_short_line_with_the_whole_headline():
+    """Every row present with all its figures: the line on stdout stays short and holds the headline."""
+    import json
+    sweep = {"GBps": 6893.123456789, "tokens_per_s": 1632.987654321, "roofline": {"traffic": 4229560908.5},
+             "batched": [{"batch": b, "tokens_per_s": 7123.456789 * b, "note": "x" * 200} for b in (1, 2, 4, 8)],
+             "batched_matrix_cores": [{"batch": b, "tokens_per_s": 17123.456789} for b in (1, 2, 4, 8, 16)]}
+    rows = {"probe": {"resident_GBps": 7000.123456, "mapped_GBps": 55.123456, "roofline": {"note": "x" * 500}},
+            "gemv_f16": {"us_per_gemv": 6.5123456, "GBps_per_dispatch": 5152.3, "one_launch_32_matrices_GBps": 6812.3},
+            "llama8b_q4": sweep,
+            "protocol": dict(sweep, one_launch_back_to_back={"GBps_at_median": 6912.3}, dispatches_12={"GBps_at_median": 5612.3}),
+            "endpoints": {"GBps": {"map_pinned_in_place": 55.1, "resident": 6901.2, "copy_from_file_pages": 50.2, "copy_from_pinned": 52.3},
+                          "alg2": {"choice": "resident", "theta_sweep": {}}},
+            "ordering": {"results": {f"{w}/{d}": {"excess": {"event": {"median_ms": 0.0982}}} for w in ("mm", "small") for d in (2, 8, 32)}},
+            "size_sweep": {"crossovers": {"resident_plateau_GBps": 7012.3}, "points": [{"resident_us": 3.4}] * 12},
+            "bus": {"h2d_GBps": 57.3}}
+    record = {"metric": "achieved GB/s (% of HBM peak) for decode-step GEMV sweep; tokens/s at batch 1", "value": 7204.11,
+              "unit": "GB/s", "n_gpus": 1, "steps": 20, "warmup": 5, "ms_per_step": 19.3012, "higher_is_better": True,
+              "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic", "config": {"step": "x" * 200},
+              "tokens_per_s": 51.8, "hbm_frac": 0.9005, "roofline": {"bound": "hbm", "traffic": 141645873511.2},
+              "probe_ceiling": {"GBps": 7000.1, "frac": 1.03, "note": "x" * 300},
+              "cpu_baseline": {"value": 10.1, "unit": "GB/s", "cores": 16, "kind": "oracle", "sample": "x" * 300},
+              "parity": {"worst_rel_l2": 1e-6, "rows": ["x"] * 100}, "passes": {"n": 5, "median": 19.3, "iqr": [19.2, 19.4],
+              "ms_per_token": [19.3] * 5}, "rows": rows, "wall_s": 60.0}
+    text = bench.short_line(record)
+    assert "\n" not in text and len(text) <= bench.LINE_MAX
+    line = json.loads(text)
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+              "dtype", "data", "config"):
+        assert line[k] == record[k], k
+    assert set(line["rows"]) == set(rows)                       # all of them fit
+    assert line["rows"]["llama8b_q4"]["matrix_cores16_tok_s"] == 17123.5 and line["passes"]["median"] == 19.3
+    record["rows"]["endpoints"]["GBps"] = {"k" * 40 + str(i): 1.0 for i in range(60)}
+    assert len(bench.short_line(record)) <= bench.LINE_MAX       # and a row that does not is left out
