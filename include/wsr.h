@@ -225,7 +225,8 @@ wsr_status wsr_decode_sweep_noalloc(const wsr_mat* mats, int32_t n, int32_t n_to
    products are added in the matrix core's own order, so outputs agree with wsr_decode_sweep within
    rounding (not bit for bit: relative L2 within 1e-5 per matrix over 16 tokens on the tested
    models, up to about 1.2e-5 for single tokens of 14,336-long q4 rows); a unit activation vector
-   still returns the dequantised weights exactly.  Tokens go in passes of 16, the
+   still returns the dequantised weights exactly.  A matrix's outputs are the same bits whatever else
+   the table holds.  Tokens go in passes of 16, the
    last pass holding the rest.  A pass of a single token (n_tokens = 1, or a last pass of one) runs
    the vector-ALU loop of wsr_decode_sweep instead, whose outputs it then equals bit for bit: a
    matrix instruction would compute 16 token slots to use one.  Formats, layouts, flags and the workspace as for wsr_decode_sweep;

@@ -93,7 +93,11 @@ static int64_t rounds_of(const DevMat* m, int nmat, int64_t rows) {
      bf16 16 columns 16.4 18.6 / 25.7 25.7  23.9 22.6 / 37.4 26.9  27.8 28.9 / 46.4 39.1  40.4 29.1 / 68.1 41.1  41.6 37.5 / 70.5 44.3
    16-bit weights with at most four columns, whose activations are half their weights' size or less, stay
    with the split form on long streams too (four layers and the head of the 70B model in bf16 at 2
-   columns: 1.37, 1.46 ms per pass, at 4 1.38, 1.46). */
+   columns: 1.37, 1.46 ms per pass, at 4 1.38, 1.46).
+   Tables of several formats always take k_cols, which replaced claimed tiles on the vector ALUs (us a
+   pass at 2, 4 and 8 columns, before and now: four layers each in q4, int8 and f16, 4096 and 14336
+   wide, 885 -> 523, 1,074 -> 541, 1,826 -> 632; two of each 2048 and 5632 wide, and a head, 176 -> 91,
+   201 -> 92, 300 -> 125). */
 static bool cols_split(int fmt, int T, int64_t rounds32) {
     const bool w16 = fmt == FMT_F16 || fmt == FMT_BF16;
     if (w16 && T <= 4) return true;

@@ -45,7 +45,6 @@ __device__ __forceinline__ u32x4 load_once(g_u32x4* p) { return __builtin_nontem
 __device__ __forceinline__ u32x4 load_reused(g_u32x4* p) { return *p; }
 __device__ __forceinline__ u32x4 zero4() { return u32x4{0u, 0u, 0u, 0u}; }
 
-/* The wave's index inside its block, as a uniform (scalar) value. */
 /* Raw buffer access: a wave-uniform base in a scalar resource, a 32-bit lane offset, a scalar
    offset and an immediate, with no per-lane address arithmetic.  Every access here is in bounds
    by construction, so the resource's range check is left open (num_records = 2^32 - 1); the word
@@ -80,6 +79,7 @@ __device__ __forceinline__ const char* uniform_ptr(const char* p) {
     return reinterpret_cast<const char*>(hi << 32 | lo);
 }
 
+/* The wave's index inside its block, as a uniform (scalar) value. */
 __device__ __forceinline__ int wave_in_block() {
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
 }

@@ -12,9 +12,8 @@
  * Streaming layout.  HBM3E serves long sequential runs best.  Each probe block walks its own
  * contiguous region.  The sweeps give each wave an equal contiguous span of the weight stream, and far
  * more blocks than the chip holds, so that retiring blocks are replaced up to the end.  16-bit streams
- * of 64 GiB and mixed tables hand out tiles of the stream (64 KiB to 2 MiB) in
- * order from a counter, so the waves in flight work on one moving front of memory and finish
- * together.
+ * of 64 GiB or more and mixed tables hand out tiles of the stream (64 KiB to 2 MiB) in order from a
+ * counter, so the waves in flight work on one moving front of memory and finish together.
  */
 #include <hip/hip_runtime.h>
 

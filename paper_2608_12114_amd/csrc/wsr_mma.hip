@@ -26,8 +26,14 @@ constexpr int64_t SWEEP_SPAN_MMA = 64 << 10;  /* least bytes of the weight strea
    1,582 -> 1,354 at 4; 72B int8 918 -> 855 and 778 -> 745; a 1.2 GB bf16 model of 2,048-wide layers
    258 -> 210; an 8B bf16 layer as a chain of four launches 289 -> 139.  With two waves 1,468, 918, 231 and
    169; with eight 1,405, 874, 227 and 143; four waves with groups of 128 rows, one wave per SIMD, 1,487,
-   843, 230 and 216 (and 193 against 180 on equal int8 rows of 7,168, where one wave had 178).  q4 rows are short (2 to 8 KiB) and their passes bound by decoding: one wave, and
-   one for mixed tables, which hold the q4 loops. */
+   843, 230 and 216.  What it costs: int8 at 13 to 16 tokens reads the activations once per 64 rows where
+   one wave read them once per 128, and equal matrices whose 128-row groups came out even over the
+   CUs were faster so (at 16 tokens twelve of 12288 x 7168 181, now 190; 24 of 4096 x 14336 217, now 241;
+   128256 x 8192 168 to 187, now 168 to 180); with other sizes and in models they were slower (32 of 4096
+   x 4096 128, now 103; 48 of 4096 x 14336 527, now 477; 8B layers 435, now 366).  q4 rows are short (2 to
+   8 KiB) and their passes bound by decoding: one wave, and one for mixed tables, which hold the q4
+   loops (it sums 16-bit and int8 rows in the same parts, 0.5 % slower than in one: int8 and f16 8B
+   layers 520 -> 522). */
 template <int FMT> constexpr int mma_split() { return FMT == FMT_F16 || FMT == FMT_BF16 || FMT == FMT_I8 ? MMA_SPLIT : 1; }
 
 /* Workgroups of mma_split(FMT) waves, few so that one whose span holds no row group frees its slots
