@@ -428,28 +428,35 @@ struct ShortTable {
     DevMat m[SHORT_MATS];
 };
 
-template <int FMT, int R, int U>
-__global__ __launch_bounds__(BLOCK) void k_sweep_short(int f1, int f2, int f3, int f4, int f5, int f6, int f7,
+template <int FMT, int R, int U, int WAVES>
+__device__ __forceinline__ void short_rows(const DevMat& d, int64_t r0, int64_t r1, int32_t token, int lane) {
+    if constexpr (FMT == FMT_Q4) {
+        rows_q4<R, U, 2>(d, r0, r1, token, lane);
+    } else if constexpr (FMT == FMT_I8 && WAVES == 1) {
+        if (d.nc % WAVE == 0) rows_i8_pipe<R, 1, I8_NB, false>(d, r0, r1, token, lane);
+        else rows_i8_pipe<R, 1, I8_NB, true>(d, r0, r1, token, lane);
+    } else if constexpr (FMT == FMT_I8) {
+        rows_i8<R>(d, r0, r1, token, lane);
+    } else {
+        rows16<FMT, R, U>(d, r0, r1, token, lane);
+    }
+}
+
+template <int FMT, int R, int U, int WAVES>
+__global__ __launch_bounds__(WAVE * WAVES) void k_sweep_short(int f1, int f2, int f3, int f4, int f5, int f6, int f7,
                                                        int32_t token, ShortTable tb) {
     const int lane = threadIdx.x & (WAVE - 1), b = (int)blockIdx.x;
     const int m = (b >= f1) + (b >= f2) + (b >= f3) + (b >= f4) + (b >= f5) + (b >= f6) + (b >= f7);
     const int first = m == 0 ? 0 : m == 1 ? f1 : m == 2 ? f2 : m == 3 ? f3 : m == 4 ? f4 : m == 5 ? f5 : m == 6 ? f6 : f7;
     const DevMat& d = tb.m[m];
-    const int64_t r0 = ((int64_t)(b - first) * WAVES_PER_BLOCK + wave_in_block()) * R;
+    const int64_t r0 = ((int64_t)(b - first) * WAVES + (WAVES == 1 ? 0 : wave_in_block())) * R;
     if (r0 >= d.M) return;
-    if (d.M - r0 >= R) {
-        if constexpr (FMT == FMT_Q4) rows_q4<R, U, 2>(d, r0, r0 + R, token, lane);
-        else if constexpr (FMT == FMT_I8) rows_i8<R>(d, r0, r0 + R, token, lane);
-        else rows16<FMT, R, U>(d, r0, r0 + R, token, lane);
-    } else {
-        if constexpr (FMT == FMT_Q4) rows_q4<1, U, 2>(d, r0, d.M, token, lane);
-        else if constexpr (FMT == FMT_I8) rows_i8<1>(d, r0, d.M, token, lane);
-        else rows16<FMT, 1, U>(d, r0, d.M, token, lane);
-    }
+    if (d.M - r0 >= R) short_rows<FMT, R, U, WAVES>(d, r0, r0 + R, token, lane);
+    else short_rows<FMT, 1, U, WAVES>(d, r0, d.M, token, lane);
 }
 
-template <int FMT, int R, int U>
-static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipStream_t s) {
+template <int FMT, int R, int U, int WAVES>
+static hipError_t launch_short_blocks(const DevMat* htab, int nmat, int32_t token, hipStream_t s) {
     ShortTable tb;
     int f[SHORT_MATS + 1];
     int64_t blocks = 0;
@@ -457,11 +464,38 @@ static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipS
         f[i] = i < nmat ? (int)blocks : INT32_MAX;
         if (i >= nmat) continue;
         tb.m[i] = htab[i];
-        blocks += (htab[i].M + WAVES_PER_BLOCK * R - 1) / (WAVES_PER_BLOCK * R);   /* at most SHORT_ROWS / 4 */
+        blocks += (htab[i].M + WAVES * R - 1) / (WAVES * R);   /* at most SHORT_ROWS / 4 */
     }
-    hipLaunchKernelGGL((k_sweep_short<FMT, R, U>), dim3((unsigned)blocks), dim3(BLOCK), 0, s, f[1], f[2], f[3], f[4], f[5],
-                       f[6], f[7], token, tb);
+    hipLaunchKernelGGL((k_sweep_short<FMT, R, U, WAVES>), dim3((unsigned)blocks), dim3(WAVE * WAVES), 0, s, f[1], f[2], f[3],
+                       f[4], f[5], f[6], f[7], token, tb);
     return hipGetLastError();
+}
+
+/* Launches of few waves over long rows are bound by the latency of a wave's own steps and by the loads a CU
+   keeps in flight: their waves go to CUs of their own, in blocks of one, with longer steps (16-bit) or the
+   pipelined loop (int8).  us, blocks of four and of one: bf16 64 x 28672 10.0 and 7.7, 512 x 14336 6.5
+   and 6.3, but 1024 x 14336 7.2 and 7.9, and rows of 4,096 alike; int8 1024 x 14336 12.5 and 6.6, 4096 x
+   8192 10.5 and 7.8, but 8192 x 14336 19.6 and 20.1, 8192 x 2064 6.0 and 6.5.  q4, two sets of loads in
+   flight in any case, takes blocks of one for all: 8192 x 8192 11.0 and 9.0, 4096 x 4096 4.6 and 4.5,
+   4096 x 28672 12.8 and 13.1, a model 1,024 wide as a chain 135 and 133. */
+static bool short_few(const DevMat* htab, int nmat, int rows, int64_t nc_over, int64_t most) {
+    int64_t waves = 0, nc = 0;
+    for (int i = 0; i < nmat; ++i) {
+        waves += (htab[i].M + rows - 1) / rows;
+        nc = std::max(nc, htab[i].nc);
+    }
+    return nc > nc_over && waves <= most;
+}
+
+template <int FMT>
+static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipStream_t s) {
+    if constexpr (FMT == FMT_Q4) return launch_short_blocks<FMT, 4, 1, 1>(htab, nmat, token, s);
+    else if constexpr (FMT == FMT_I8)
+        return short_few(htab, nmat, 2, 256, 2048) ? launch_short_blocks<FMT, 2, 1, 1>(htab, nmat, token, s)
+                                                   : launch_short_blocks<FMT, 2, 1, WAVES_PER_BLOCK>(htab, nmat, token, s);
+    else
+        return short_few(htab, nmat, 1, 512, 512) ? launch_short_blocks<FMT, 1, 8, 1>(htab, nmat, token, s)
+                                                  : launch_short_blocks<FMT, 1, 4, WAVES_PER_BLOCK>(htab, nmat, token, s);
 }
 
 static int cu_count() {
@@ -585,10 +619,10 @@ hipError_t launch_sweep(const DevMat* tab, const int64_t* cost, const DevMat* ht
     if (nmat == 0 || total == 0) return hipSuccess;
     if (T == 1 && sweep_short(htab, nmat, total, fmt_all)) {
         switch (fmt_all) {
-            case FMT_Q4: return launch_short<FMT_Q4, 4, 1>(htab, nmat, token, s);
-            case FMT_I8: return launch_short<FMT_I8, 2, 1>(htab, nmat, token, s);
-            case FMT_F16: return launch_short<FMT_F16, 1, 4>(htab, nmat, token, s);
-            default: return launch_short<FMT_BF16, 1, 4>(htab, nmat, token, s);
+            case FMT_Q4: return launch_short<FMT_Q4>(htab, nmat, token, s);
+            case FMT_I8: return launch_short<FMT_I8>(htab, nmat, token, s);
+            case FMT_F16: return launch_short<FMT_F16>(htab, nmat, token, s);
+            default: return launch_short<FMT_BF16>(htab, nmat, token, s);
         }
     }
     const bool pair = sweep_i8_pair(htab, nmat, fmt_all, T);

@@ -96,10 +96,11 @@ static hipError_t mma_slots(int fmt_all, int64_t& slots) {
     switch (f) {
         case FMT_F16: e = occupancy_of<FMT_F16>(per_cu); break;
         case FMT_BF16: e = occupancy_of<FMT_BF16>(per_cu); break;
-        case FMT_Q4: e = occupancy_of<FMT_Q4>(per_cu); break;
         case FMT_I8: e = occupancy_of<FMT_I8>(per_cu); break;
-        case FMT_Q4_WHOLE: e = occupancy_of<FMT_Q4_WHOLE>(per_cu); break;
-        default: e = occupancy_of<0>(per_cu); break;
+        default:   /* q4 too: by its own kernels, which hold two waves per SIMD, launches of little more than a
+                      wave per SIMD would get no tail (us: 67529 x 8192 at 5 tokens 91, so 70; 81448 x 4608 at
+                      12 54 and 47; 21 of 3808 x 4096 74 and 68; the 8B model alike) */
+            e = occupancy_of<0>(per_cu); break;
     }
     if (e != hipSuccess) return e;
     slots = (int64_t)cus * per_cu;
