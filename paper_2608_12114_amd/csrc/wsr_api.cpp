@@ -893,10 +893,11 @@ extern "C" wsr_status wsr_decode_sweep_mma(const wsr_mat* mats, int32_t n, int32
     if (upload && (e = wsr::launch_put_table(dtab, dcost, p.tab.data(), n, ctr, s)) != hipSuccess)
         return hip_fail(e, "decode_sweep_mma: table upload");
     /* per segment: the largest row group of the main part and of the tail */
-    std::vector<int64_t> max_main(p.segs.size(), 0), max_tail(p.segs.size(), 0);
+    std::vector<int64_t> max_main(p.segs.size(), 0), max_tail(p.segs.size(), 0), max_row(p.segs.size(), 0);
     for (size_t i = 0; i < p.segs.size(); ++i)
         for (int m = p.segs[i].first; m < p.segs[i].first + p.segs[i].count; ++m) {
             const int64_t rb = p.tab[m].row_bytes, M = p.tab[m].M;
+            max_row[i] = std::max(max_row[i], p.tab[m].nc * 16);
             max_main[i] = std::max(max_main[i], rb * std::min<int64_t>(M, wsr::MMA_ROWS));
             max_tail[i] = std::max(max_tail[i], rb * std::min<int64_t>(M, wsr::MMA_TAIL_ROWS));
         }
@@ -917,7 +918,7 @@ extern "C" wsr_status wsr_decode_sweep_mma(const wsr_mat* mats, int32_t n, int32
             e = ntok == 1 ? wsr::launch_sweep(dtab + g.first, dcost + g.first, p.tab.data() + g.first, g.count, g.total,
                                               g.fmt, t, 1, ctr, s)
                           : wsr::launch_sweep_mma(dtab + g.first, dcost + g.first, g.count, g.total,
-                                                  max_main[i], max_tail[i], mma_fmt[i], t, ntok, s);
+                                                  max_main[i], max_tail[i], max_row[i], mma_fmt[i], t, ntok, s);
             if (e != hipSuccess) return hip_fail(e, "decode_sweep_mma: launch");
         }
     }

@@ -117,32 +117,32 @@ constexpr int64_t COLS_BLOCKS = 512, SPLIT_BLOCKS = 1024;    /* least, where the
 /* Workgroups and bytes of the stream for each: `want` of them at most, and no more than there are rounds
    of `rows` rows, since an empty one still waits for its LDS (1024 x 4096 q4 at 8 columns: 23 us with
    2,048 workgroups for its 128 rounds of 8 rows, 6.1 us with 128). */
-static hipError_t cols_grid(const DevMat* htab, int nmat, int64_t total, int64_t rows, int64_t want, dim3& g,
+static hipError_t cols_grid(const DevMat* htab, int nmat, int64_t cost, int64_t rows, int64_t want, dim3& g,
                             int64_t* span) {
     const int64_t rounds = rounds_of(htab, nmat, rows), each = (rounds + want - 1) / want;
     const int64_t blocks = (rounds + each - 1) / each;          /* the same number of rounds for each */
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     g = dim3((unsigned)blocks);
-    *span = (total + blocks - 1) / blocks;
+    *span = (cost + blocks - 1) / blocks;
     return hipSuccess;
 }
 
 template <int FMT, int TQ, int RG, int N>
-static hipError_t launch_split(const ColsTable<N>& tb, const DevMat* htab, int nmat, int64_t total, int32_t token, int T,
-                               hipStream_t s) {
+static hipError_t launch_split(const ColsTable<N>& tb, const DevMat* htab, int nmat, int64_t total, int64_t cost, int32_t token,
+                               int T, hipStream_t s) {
     const int64_t bytes = FMT == FMT_I8 ? SPLIT_SPAN_I8 : SPLIT_SPAN;
     dim3 g;
     int64_t span = 0;
-    const hipError_t e = cols_grid(htab, nmat, total, 4 * RG, std::max<int64_t>(SPLIT_BLOCKS, (total + bytes - 1) / bytes), g,
+    const hipError_t e = cols_grid(htab, nmat, cost, 4 * RG, std::max<int64_t>(SPLIT_BLOCKS, (total + bytes - 1) / bytes), g,
                                    &span);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_split<FMT, TQ, RG, N>), g, dim3(4 * WAVE), 0, s, nmat, token, total, span, T, tb);
+    hipLaunchKernelGGL((k_split<FMT, TQ, RG, N>), g, dim3(4 * WAVE), 0, s, nmat, token, cost, span, T, tb);
     return hipGetLastError();
 }
 
 template <int FMT, int TQ, int N>
-static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int nmat, int64_t total, int32_t token, int T,
-                               hipStream_t s) {
+static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int nmat, int64_t total, int64_t cost, int32_t token,
+                               int T, hipStream_t s) {
     if constexpr (FMT != 0) {
         if (cols_split(FMT, T, rounds_of(htab, nmat, COLS_ROUND))) {
             constexpr int RG = split_rg<FMT>();
@@ -150,8 +150,8 @@ static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int n
                4096 8.8 and 7.4 */
             if constexpr (N == COLS_TABLE_ARG && RG > SPLIT_RG_FEW)
                 if (rounds_of(htab, nmat, 4 * RG) <= 128)
-                    return launch_split<FMT, TQ, SPLIT_RG_FEW, N>(tb, htab, nmat, total, token, T, s);
-            return launch_split<FMT, TQ, RG, N>(tb, htab, nmat, total, token, T, s);
+                    return launch_split<FMT, TQ, SPLIT_RG_FEW, N>(tb, htab, nmat, total, cost, token, T, s);
+            return launch_split<FMT, TQ, RG, N>(tb, htab, nmat, total, cost, token, T, s);
         }
     }
     if constexpr (FMT == 0 || FMT == FMT_Q4 || FMT == FMT_I8 || TQ > 1) {    /* 16-bit, TQ = 1: always split */
@@ -160,23 +160,49 @@ static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int n
         const int64_t bytes = COLS_BLOCKS * (FMT == FMT_I8 ? COLS_SPAN_I8 : COLS_SPAN);
         dim3 g;
         int64_t span = 0;
-        const hipError_t e = cols_grid(htab, nmat, total, COLS_ROUND,
+        const hipError_t e = cols_grid(htab, nmat, cost, COLS_ROUND,
                                        COLS_BLOCKS * std::max<int64_t>(1, (total + bytes / 2) / bytes), g, &span);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_cols<FMT, TQ, WAVES, N>), g, dim3(WAVE * WAVES), 0, s, nmat, token, total, span, T, tb);
+        hipLaunchKernelGGL((k_cols<FMT, TQ, WAVES, N>), g, dim3(WAVE * WAVES), 0, s, nmat, token, cost, span, T, tb);
         return hipGetLastError();
     }
     return hipErrorInvalidValue;
 }
 
+/* Whether the rows of a table by value are weighed by their steps (of 64 chunks, and one more for the join
+   and the start) instead of their bytes: where the shortest are a few chunks long, equal bytes give some
+   workgroups hundreds of rounds of short rows, each with its own latency (us a pass, by bytes and by
+   steps: q4 at 4 columns 115 x 512, 2000 x 64 and 609 x 11008 62 and 9.2; f16 at 4 892 x 8192, 5000 x 64,
+   20000 x 256 and 7272 x 28672 314 and 107; bf16 at 2 6777 x 88, 60000 x 7000 and 4655 x 7352 516 and 180).
+   Long rows stream at their bytes: where the lengths differ by up to four, as in a model's layers,
+   weighing by steps costs up to a third (layers of 2,048 and 5,632 in q4 at 8 columns 53.5 and 67.7, int8
+   8B layers at 4 148.5 and 172.6). */
+constexpr int64_t COLS_STEPS_FROM = 4;
+static bool cols_by_steps(const DevMat* htab, int nmat) {
+    int64_t lo = INT64_MAX, hi = 0;
+    for (int i = 0; i < nmat; ++i) {
+        if (htab[i].M == 0) continue;
+        lo = std::min(lo, htab[i].nc);
+        hi = std::max(hi, htab[i].nc);
+    }
+    return COLS_STEPS_FROM * lo < hi;
+}
+
 template <int FMT, int TQ, int N>
 static hipError_t launch_arg(const DevMat* htab, int nmat, int64_t total, int32_t token, int T, hipStream_t s) {
     ColsTable<N> tb;
+    const bool steps = cols_by_steps(htab, nmat);
+    int64_t cost = 0;
     for (int i = 0; i < nmat; ++i) {
         tb.m_[i] = htab[i];
-        tb.cost_[i] = htab[i].cost0;
+        if (steps) {
+            tb.m_[i].cost0 = cost;
+            tb.m_[i].row_bytes = (htab[i].nc + WAVE - 1) / WAVE + 1;
+            cost += tb.m_[i].row_bytes * htab[i].M;
+        }
+        tb.cost_[i] = tb.m_[i].cost0;
     }
-    return launch_table<FMT, TQ, N>(tb, htab, nmat, total, token, T, s);
+    return launch_table<FMT, TQ, N>(tb, htab, nmat, total, steps ? cost : total, token, T, s);
 }
 
 template <int FMT, int TQ>
@@ -187,7 +213,7 @@ static hipError_t launch_q(const DevMat* tab, const int64_t* cost, const DevMat*
         if (nmat <= COLS_TABLE_ARG_MID) return launch_arg<FMT, TQ, COLS_TABLE_ARG_MID>(htab, nmat, total, token, T, s);
         if (nmat <= COLS_TABLE_ARG_MAX) return launch_arg<FMT, TQ, COLS_TABLE_ARG_MAX>(htab, nmat, total, token, T, s);
     }
-    return launch_table<FMT, TQ, 0>({tab, cost}, htab, nmat, total, token, T, s);
+    return launch_table<FMT, TQ, 0>({tab, cost}, htab, nmat, total, total, token, T, s);
 }
 
 template <int FMT>

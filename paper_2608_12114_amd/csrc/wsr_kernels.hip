@@ -474,27 +474,29 @@ static hipError_t launch_short_blocks(const DevMat* htab, int nmat, int32_t toke
 /* Launches of few waves over long rows are bound by the latency of a wave's own steps and by the loads a CU
    keeps in flight: their waves go to CUs of their own, in blocks of one, with longer steps (16-bit) or the
    pipelined loop (int8).  us, blocks of four and of one: bf16 64 x 28672 10.0 and 7.7, 512 x 14336 6.5
-   and 6.3, but 1024 x 14336 7.2 and 7.9, and rows of 4,096 alike; int8 1024 x 14336 12.5 and 6.6, 4096 x
+   and 6.3, 17 x 28672 beside 625 x 10496 11.2 and 8.8, but 768 x 14336 6.8 and 7.1, 1024 x 14336 7.2
+   and 7.9, 8192 x 2048 6.7 and 7.2, and rows of 4,096 alike; int8 1024 x 14336 12.5 and 6.6, 4096 x
    8192 10.5 and 7.8, but 8192 x 14336 19.6 and 20.1, 8192 x 2064 6.0 and 6.5.  q4, two sets of loads in
    flight in any case, takes blocks of one for all: 8192 x 8192 11.0 and 9.0, 4096 x 4096 4.6 and 4.5,
    4096 x 28672 12.8 and 13.1, a model 1,024 wide as a chain 135 and 133. */
-static bool short_few(const DevMat* htab, int nmat, int rows, int64_t nc_over, int64_t most) {
-    int64_t waves = 0, nc = 0;
+static bool short_few(const DevMat* htab, int nmat, int rows, int64_t nc_over, int64_t most_long, int64_t most) {
+    int64_t waves = 0, of_long = 0;
     for (int i = 0; i < nmat; ++i) {
-        waves += (htab[i].M + rows - 1) / rows;
-        nc = std::max(nc, htab[i].nc);
+        const int64_t n = (htab[i].M + rows - 1) / rows;
+        waves += n;
+        if (htab[i].nc > nc_over) of_long += n;
     }
-    return nc > nc_over && waves <= most;
+    return of_long > 0 && of_long <= most_long && waves <= most;
 }
 
 template <int FMT>
 static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipStream_t s) {
     if constexpr (FMT == FMT_Q4) return launch_short_blocks<FMT, 4, 1, 1>(htab, nmat, token, s);
     else if constexpr (FMT == FMT_I8)
-        return short_few(htab, nmat, 2, 256, 2048) ? launch_short_blocks<FMT, 2, 1, 1>(htab, nmat, token, s)
+        return short_few(htab, nmat, 2, 256, 2048, 4096) ? launch_short_blocks<FMT, 2, 1, 1>(htab, nmat, token, s)
                                                    : launch_short_blocks<FMT, 2, 1, WAVES_PER_BLOCK>(htab, nmat, token, s);
     else
-        return short_few(htab, nmat, 1, 512, 512) ? launch_short_blocks<FMT, 1, 8, 1>(htab, nmat, token, s)
+        return short_few(htab, nmat, 1, 512, 768, 2048) ? launch_short_blocks<FMT, 1, 8, 1>(htab, nmat, token, s)
                                                   : launch_short_blocks<FMT, 1, 4, WAVES_PER_BLOCK>(htab, nmat, token, s);
 }
 

@@ -34,20 +34,30 @@ constexpr int64_t SWEEP_SPAN_MMA = 64 << 10;  /* least bytes of the weight strea
    8 KiB) and their passes bound by decoding: one wave, and one for mixed tables, which hold the q4
    loops (it sums 16-bit and int8 rows in the same parts, 0.5 % slower than in one: int8 and f16 8B
    layers 520 -> 522). */
-template <int FMT> constexpr int mma_split() { return FMT == FMT_F16 || FMT == FMT_BF16 || FMT == FMT_I8 ? MMA_SPLIT : 1; }
+/* Rows of two to four steps for each of the four waves leave little to split and still pay for the joins:
+   streams of MMA_WHOLE_FROM bytes and more of such rows alone go one wave per workgroup, which sums the
+   same parts.  us, four waves and one: int8 30 of 15536 x 96 39.3 and 25.6, of 15536 x 1024 105 and 82,
+   24 of 2048 x 1024 (50 MB) 18.8 and 15.2, of 15536 x 2048 at 3 and 16 tokens 170 and 160, 193 and 192, of
+   15536 x 3072 224 and 238; bf16 30 of 15536 x 512 94 and 80, of 15536 x 768 114 and 120; but 25 MB: int8
+   24 of 2048 x 512 14.1 and 15.6, 100000 x 256 14.2 and 16.4; bf16 24 of 2048 x 256 11.5 and 12.5. */
+constexpr int64_t MMA_WHOLE_FROM = 40 << 20;
+static bool mma_splits(int fmt_all, int64_t max_row, int64_t total) {
+    if (fmt_all != FMT_F16 && fmt_all != FMT_BF16 && fmt_all != FMT_I8) return false;
+    return max_row > (fmt_all == FMT_I8 ? 2048 : 1024) || total < MMA_WHOLE_FROM;
+}
 
-/* Workgroups of mma_split(FMT) waves, few so that one whose span holds no row group frees its slots
+/* Workgroups of KS waves, few so that one whose span holds no row group frees its slots
    at once.  Workgroups w < w1 split the stream's bytes [0, tail) into equal spans of whole row groups
    of MMA_ROWS rows; the others split [tail, total) into spans of 16-row groups.  The launcher sets a
    tail only where the main spans would leave the last round of workgroup slots at most a quarter full;
    then the last to finish hold a quarter of a group's work or less.  A matrix's rows from the first
    main-group boundary at or after byte `tail` on belong to the tail, the rows before it to the main
    spans. */
-template <int FMT>
-__global__ __launch_bounds__(WAVE * mma_split<FMT>()) __attribute__((amdgpu_waves_per_eu(FMT == FMT_Q4_WHOLE ? 2 : 1)))
+template <int FMT, int KS>
+__global__ __launch_bounds__(WAVE * KS) __attribute__((amdgpu_waves_per_eu(FMT == FMT_Q4_WHOLE || (KS == 1 && FMT != 0 && FMT != FMT_Q4) ? 2 : 1)))
 void k_sweep_mma(const DevMat* __restrict__ tab, const int64_t* __restrict__ cost, int nmat, int64_t total,
                  int64_t tail, int64_t w1, int32_t token0, int ntok) {
-    constexpr int NT = MMA_TILES, KS = mma_split<FMT>();
+    constexpr int NT = MMA_TILES;
     const int lane = threadIdx.x & (WAVE - 1), wave = KS == 1 ? 0 : wave_in_block();
     const int64_t w = blockIdx.x;
     const bool main = w < w1;
@@ -72,44 +82,44 @@ void k_sweep_mma(const DevMat* __restrict__ tab, const int64_t* __restrict__ cos
                                                   hint, ring, joins);
 }
 
-template <int FMT>
+template <int FMT, int KS>
 static hipError_t occupancy_of(int& per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_mma<FMT>, WAVE * mma_split<FMT>(), 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_mma<FMT, KS>, WAVE * KS, 0);
 }
 
 /* Workgroup slots of the device for the kernel of format fmt_all (its occupancy times the CU count),
    found once per device and format. */
-static hipError_t mma_slots(int fmt_all, int64_t& slots) {
+static hipError_t mma_slots(int fmt_all, bool split, int64_t& slots) {
     static std::mutex mu;
-    static int64_t cache[64][9] = {};
+    static int64_t cache[64][2][9] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const int f = (fmt_all >= 0 && fmt_all <= 4) || fmt_all == FMT_Q4_WHOLE ? fmt_all : 0;
     std::lock_guard<std::mutex> lock(mu);
-    if (dev >= 0 && dev < 64 && cache[dev][f] > 0) {
-        slots = cache[dev][f];
+    if (dev >= 0 && dev < 64 && cache[dev][split][f] > 0) {
+        slots = cache[dev][split][f];
         return hipSuccess;
     }
     int cus = 0, per_cu = 0;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
     switch (f) {
-        case FMT_F16: e = occupancy_of<FMT_F16>(per_cu); break;
-        case FMT_BF16: e = occupancy_of<FMT_BF16>(per_cu); break;
-        case FMT_I8: e = occupancy_of<FMT_I8>(per_cu); break;
+        case FMT_F16: e = split ? occupancy_of<FMT_F16, MMA_SPLIT>(per_cu) : occupancy_of<FMT_F16, 1>(per_cu); break;
+        case FMT_BF16: e = split ? occupancy_of<FMT_BF16, MMA_SPLIT>(per_cu) : occupancy_of<FMT_BF16, 1>(per_cu); break;
+        case FMT_I8: e = split ? occupancy_of<FMT_I8, MMA_SPLIT>(per_cu) : occupancy_of<FMT_I8, 1>(per_cu); break;
         default:   /* q4 too: by its own kernels, which hold two waves per SIMD, launches of little more than a
                       wave per SIMD would get no tail (us: 67529 x 8192 at 5 tokens 91, so 70; 81448 x 4608 at
                       12 54 and 47; 21 of 3808 x 4096 74 and 68; the 8B model alike) */
-            e = occupancy_of<0>(per_cu); break;
+            e = occupancy_of<0, 1>(per_cu); break;
     }
     if (e != hipSuccess) return e;
     slots = (int64_t)cus * per_cu;
-    if (dev >= 0 && dev < 64) cache[dev][f] = slots;
+    if (dev >= 0 && dev < 64) cache[dev][split][f] = slots;
     return hipSuccess;
 }
 
 hipError_t launch_sweep_mma(const DevMat* tab, const int64_t* cost, int nmat, int64_t total, int64_t max_group,
-                            int64_t max_tail_group, int fmt_all, int32_t token0, int ntok, hipStream_t s) {
+                            int64_t max_tail_group, int64_t max_row, int fmt_all, int32_t token0, int ntok, hipStream_t s) {
     if (nmat == 0 || total == 0) return hipSuccess;
     if (ntok < 1 || ntok > MMA_TOKENS) return hipErrorInvalidValue;
     /* a workgroup's span holds at least the largest row group: a row group is never split, so a smaller
@@ -117,8 +127,9 @@ hipError_t launch_sweep_mma(const DevMat* tab, const int64_t* cost, int nmat, in
     const int64_t span = std::max(SWEEP_SPAN_MMA, max_group);
     const int64_t span_t = std::max(SWEEP_SPAN_MMA / 4, max_tail_group);
     const int64_t waves = (total + span - 1) / span;
+    const bool split = mma_splits(fmt_all, max_row, total);
     int64_t slots = 0;
-    const hipError_t e = mma_slots(fmt_all, slots);
+    const hipError_t e = mma_slots(fmt_all, split, slots);
     if (e != hipSuccess) return e;
     /* whole rounds of spans, and a tail only where the last round would be at most a quarter full
        (measured on int8 passes: 1/8 full 323 -> 265 us per pass with the tail; 1/2 full 356 -> 381) */
@@ -130,17 +141,20 @@ hipError_t launch_sweep_mma(const DevMat* tab, const int64_t* cost, int nmat, in
         w2 = (total - tail + span_t - 1) / span_t;
     }
     if (w1 + w2 > INT32_MAX) return hipErrorInvalidValue;
-#define WSR_MMA(F)                                                                                              \
-    hipLaunchKernelGGL((k_sweep_mma<F>), dim3((unsigned)(w1 + w2)), dim3(WAVE * mma_split<F>()), 0, s, tab, cost, \
-                       nmat, total, tail, w1, token0, ntok)
+#define WSR_MMA(F, KS)                                                                                              \
+    hipLaunchKernelGGL((k_sweep_mma<F, KS>), dim3((unsigned)(w1 + w2)), dim3(WAVE * KS), 0, s, tab, cost, nmat, total, \
+                       tail, w1, token0, ntok)
+#define WSR_MMA_SPLIT(F) \
+    if (split) WSR_MMA(F, MMA_SPLIT); else WSR_MMA(F, 1)
     switch (fmt_all) {
-        case FMT_F16: WSR_MMA(FMT_F16); break;
-        case FMT_BF16: WSR_MMA(FMT_BF16); break;
-        case FMT_Q4: WSR_MMA(FMT_Q4); break;
-        case FMT_I8: WSR_MMA(FMT_I8); break;
-        case FMT_Q4_WHOLE: WSR_MMA(FMT_Q4_WHOLE); break;
-        default: WSR_MMA(0); break;
+        case FMT_F16: WSR_MMA_SPLIT(FMT_F16); break;
+        case FMT_BF16: WSR_MMA_SPLIT(FMT_BF16); break;
+        case FMT_Q4: WSR_MMA(FMT_Q4, 1); break;
+        case FMT_I8: WSR_MMA_SPLIT(FMT_I8); break;
+        case FMT_Q4_WHOLE: WSR_MMA(FMT_Q4_WHOLE, 1); break;
+        default: WSR_MMA(0, 1); break;
     }
+#undef WSR_MMA_SPLIT
 #undef WSR_MMA
     return hipGetLastError();
 }

@@ -19,9 +19,9 @@ constexpr int MMA_ROWS = 64, MMA_TAIL_ROWS = 16;
 
 /* Tokens token0 .. token0 + ntok - 1 (ntok <= 16) of the sweep on the matrix cores; max_group and
    max_tail_group are the largest row group's weight-stream bytes (MMA_ROWS rows, and MMA_TAIL_ROWS
-   rows, of any matrix in the table). */
+   rows, of any matrix in the table), max_row the longest row's weight or code bytes. */
 hipError_t launch_sweep_mma(const DevMat* tab, const int64_t* cost, int nmat, int64_t total, int64_t max_group,
-                            int64_t max_tail_group, int fmt_all, int32_t token0, int ntok, hipStream_t s);
+                            int64_t max_tail_group, int64_t max_row, int fmt_all, int32_t token0, int ntok, hipStream_t s);
 
 }  // namespace wsr
 

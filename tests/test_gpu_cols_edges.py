@@ -132,6 +132,31 @@ def test_one_pass_over_matrices_sharing_activations(n):
         assert np.array_equal(a, f32_bits(y.cpu().numpy()))
 
 
+@pytest.mark.parametrize("fmt,T", [(f, T) for f in (wl.F16, wl.BF16, wl.Q4, wl.I8) for T in (2, 4, 8, 16)
+                                   if T <= 8 or f in (wl.F16, wl.BF16)])
+@pytest.mark.parametrize("n", [5, 20])
+def test_rows_of_very_unequal_lengths(fmt, T, n):
+    """Tables whose rows are weighed by their steps, among them empty rows and a matrix of no rows; rounds for
+    both kernels."""
+    shapes = ([(700, UNIT[fmt] * 2), (33, STEP[fmt] * 9 + UNIT[fmt]), (0, 64), (45, 0), (20000, UNIT[fmt] * 5)] * 4)[:n]
+    xfmt = wl.BF16 if fmt == wl.BF16 else wl.F16
+    X = dv.to_device(synth.normal16((T, STEP[fmt] * 10), wl.X_SIGMA, xfmt, seed=33, stream=710))
+    z = zeros_u8(256)
+    made = {mk: matrix(fmt, *mk, seed=34) if mk[0] * mk[1] else (z, zeros_u8(2 * 256)) for mk in set(shapes)}
+    made = {mk: (w, dv.to_device(synth.i8_scales(mk[0], seed=34, stream=702)) if fmt == wl.I8 and mk[0] else s)
+            for mk, (w, s) in made.items()}
+    outs = [[torch.full((T, M + 1), float("nan"), dtype=torch.float32, device="cuda") for M, _ in shapes] for _ in range(2)]
+    for y, batch in zip(outs, (1, T)):
+        mats = wsr.make_mats([dict(fmt=FMT[fmt], M=M, K=K, w=made[M, K][0], scales=made[M, K][1], x=X, x_tok_stride=2 * X.shape[1],
+                                   y=y[i], y_tok_stride=4 * (M + 1)) for i, (M, K) in enumerate(shapes)])
+        ws = zeros_u8(wsr.wsr_sweep_workspace_bytes(mats))
+        wsr.wsr_decode_sweep_batched(mats, T, batch, ws, ws.numel(), stream())
+    torch.cuda.synchronize()
+    for (M, K), a, b in zip(shapes, *outs):
+        assert torch.isnan(b[:, M]).all() and not torch.isnan(b[:, :M]).any()
+        assert torch.equal(a[:, :M].contiguous().view(torch.int32), b[:, :M].contiguous().view(torch.int32)), (M, K)
+
+
 @pytest.mark.parametrize("fmt", [wl.F16, wl.BF16])
 @pytest.mark.parametrize("T,M", [(4, 40), (16, 40), (16, 32 * 300)])
 def test_values_at_the_ends_of_16_bit_formats(fmt, T, M):

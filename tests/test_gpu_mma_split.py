@@ -86,3 +86,21 @@ def test_empty_rows_give_empty_sums(fmts):
     entries = [(fmt, M, 0, any16, any16 if fmt in (wl.Q4, wl.I8) else None, any16) for fmt in fmts for M in (1, 64, 150)]
     for y in mma_table(entries, 3):
         assert not y.any()
+
+
+@pytest.mark.parametrize("fmt,K", [(wl.I8, 96), (wl.I8, 512), (wl.I8, 2048), (wl.F16, 48), (wl.BF16, 512), (wl.BF16, 520)])
+def test_long_streams_of_short_rows(fmt, K):
+    """Streams of 40 MiB and more whose rows all hold few steps go one wave per workgroup: the bits of the
+    same rows in a short stream, which four waves share."""
+    T, row = 5, K if fmt == wl.I8 else 2 * K
+    M = (41 << 20) // 3 // row // 64 * 64 + 70
+    g = torch.Generator(device="cuda").manual_seed(K)
+    W = torch.randn((3 * M, K), device="cuda", generator=g)
+    W = (W * 40).to(torch.int8) if fmt == wl.I8 else W.to(torch.bfloat16 if fmt == wl.BF16 else torch.float16)
+    S = torch.rand(3 * M, device="cuda", generator=g).to(torch.float16) if fmt == wl.I8 else None
+    X = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16 if fmt == wl.BF16 else torch.float16)
+    part = lambda r0, n: (fmt, n, K, W[r0:r0 + n], None if S is None else S[r0:r0 + n], X)  # noqa: E731
+    long = mma_table([part(i * M, M) for i in range(3)], T)
+    for i in range(3):
+        assert np.array_equal(long[i][:, :200], mma_table([part(i * M, 200)], T)[0])
+        assert np.array_equal(long[i][:, M - 134:], mma_table([part(i * M + M - 134, 134)], T)[0])

@@ -26,7 +26,7 @@ def test_more_empty_rows_than_a_grid_of_row_groups_holds(fmt, M):
     assert not y[:M].any().item()
 
 
-@pytest.mark.parametrize("fmt,M,K", [(wsr.WSR_BF16, 512, 4104), (wsr.WSR_BF16, 513, 4104), (wsr.WSR_F16, 512, 4096),
+@pytest.mark.parametrize("fmt,M,K", [(wsr.WSR_BF16, 768, 4104), (wsr.WSR_BF16, 769, 4104), (wsr.WSR_F16, 512, 4096),
                                      (wsr.WSR_F16, 3, 28680), (wsr.WSR_I8, 4096, 4112), (wsr.WSR_I8, 4097, 4112),
                                      (wsr.WSR_I8, 4096, 4096), (wsr.WSR_I8, 5, 28672), (wsr.WSR_I8, 1, 5136), (wsr.WSR_Q4, 7, 28672),
                                      (wsr.WSR_Q4, 4099, 544)])
