@@ -91,6 +91,14 @@ static int64_t rounds_of(const DevMat* m, int nmat, int64_t rows) {
      int8 8 columns  10.5 11.6 / 24.5 27.7  11.9 12.8 / 26.6 30.6  16.1 16.5 / 39.0 42.7  19.2 17.4 / 48.0 45.3  21.5 19.1 / 52.9 48.6
      bf16 8 columns  13.4 17.3 / 36.1 44.1  17.6 21.7 / 47.9 47.6  21.2 28.3 / 67.6 69.2  26.1 29.4 / 87.6 76.5  27.3 34.3 / 91.0 88.1
      bf16 16 columns 16.4 18.6 / 25.7 25.7  23.9 22.6 / 37.4 26.9  27.8 28.9 / 46.4 39.1  40.4 29.1 / 68.1 41.1  41.6 37.5 / 70.5 44.3
+   Just above 512 rounds k_cols runs a second round of workgroups that is mostly empty, and the split form
+   wins again up to about one and a half where rows are long or columns few (K = 4096 / 16384):
+     rounds            576                    704                    768                    832
+     q4   2 columns    15  16 /  49  52       16  16 /  49  53       16  16 /  52  53       19  17 /  63  54
+     q4   8 columns    23  22 /  67  84       24  22 /  69  84       24  22 /  69  85       29  23 /  85  85
+     int8 4 columns    20  22 /  73  73       20  23 /  74  77       21  24 /  77  78       25  25 /  92  80
+     int8 8 columns    23  23 /  81  86       24  24 /  86  89       25  25 /  85  92       32  26 / 106  92
+     bf16 8 columns    30  41 / 105 137       38  41 / 140 155       39  40 / 144 140       50  41 / 195 150
    16-bit weights with at most four columns, whose activations are half their weights' size or less, stay
    with the split form on long streams too (four layers and the head of the 70B model in bf16 at 2
    columns: 1.37, 1.46 ms per pass, at 4 1.38, 1.46).
@@ -98,14 +106,24 @@ static int64_t rounds_of(const DevMat* m, int nmat, int64_t rows) {
    pass at 2, 4 and 8 columns, before and now: four layers each in q4, int8 and f16, 4096 and 14336
    wide, 885 -> 523, 1,074 -> 541, 1,826 -> 632; two of each 2048 and 5632 wide, and a head, 176 -> 91,
    201 -> 92, 300 -> 125). */
-static bool cols_split(int fmt, int T, int64_t rounds32) {
-    const bool w16 = fmt == FMT_F16 || fmt == FMT_BF16;
+static bool cols_split(int fmt, int T, int64_t rounds32, int64_t steps) {   /* steps of the longest row */
+    const bool w16 = fmt == FMT_F16 || fmt == FMT_BF16, i8 = fmt == FMT_I8;
     if (w16 && T <= 4) return true;
-    return T > 8 ? rounds32 < 256 : rounds32 <= (fmt == FMT_I8 && T <= 4 ? 512 : 384);
+    if (T > 8) return rounds32 < 256;
+    if (rounds32 <= 512) return rounds32 <= (i8 && T <= 4 ? 512 : 384);
+    return rounds32 <= (w16 ? 576 : i8 && T <= 4 ? 704 : 768) && (w16 || T <= 4 || steps >= (i8 ? 8 : 4));
+}
+static int64_t longest_steps(const DevMat* m, int nmat) {
+    int64_t nc = 0;
+    for (int i = 0; i < nmat; ++i) nc = std::max(nc, m[i].nc);
+    return (nc + WAVE - 1) / WAVE;
 }
 
 bool cols_takes_split(const DevMat* htab, int nmat, int fmt_all, int T) {
-    return cols_split(fmt_all, T, rounds_of(htab, nmat, COLS_ROUND));
+    const int64_t rounds = rounds_of(htab, nmat, COLS_ROUND);
+    if (fmt_all == FMT_I8 && T == 2) return rounds <= 512;      /* above, two columns stay with the vector ALUs
+                                                                   (640 rounds of 8,192: 28.9 us, split 33.1) */
+    return cols_split(fmt_all, T, rounds, longest_steps(htab, nmat));
 }
 
 /* Bytes per workgroup: k_cols keeps its activations over a span, and longer spans balance worse
@@ -144,7 +162,7 @@ template <int FMT, int TQ, int N>
 static hipError_t launch_table(const ColsTable<N>& tb, const DevMat* htab, int nmat, int64_t total, int64_t cost, int32_t token,
                                int T, hipStream_t s) {
     if constexpr (FMT != 0) {
-        if (cols_split(FMT, T, rounds_of(htab, nmat, COLS_ROUND))) {
+        if (cols_split(FMT, T, rounds_of(htab, nmat, COLS_ROUND), longest_steps(htab, nmat))) {
             constexpr int RG = split_rg<FMT>();
             /* us, with two and with four groups per round: q4 at 8 columns 1024 x 4096 6.1 and 7.2, 4096 x
                4096 8.8 and 7.4 */

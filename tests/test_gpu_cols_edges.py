@@ -62,12 +62,19 @@ def test_short_streams(fmt, T, chunks):
                                          (wl.I8, 4, 9), (wl.I8, 8, 4), (wl.I8, 8, 5), (wl.BF16, 8, 10), (wl.BF16, 8, 11),
                                          (wl.F16, 16, 5), (wl.F16, 16, 6), (wl.F16, 16, 1)])
 def test_long_streams(fmt, T, steps):
-    """Enough rounds of 32 rows (over 384; over 512 for int8 with four columns) for the kernel that shares
+    """Enough rounds of 32 rows (384 to 512; over 704 for int8 with four columns) for the kernel that shares
     activations through LDS: rows that stay there whole and rows one step too long, with a last step
     of 64, 1 and 33 chunks, and a ragged last round."""
-    rounds = 520 if fmt == wl.I8 and T <= 4 else 400
+    rounds = 710 if fmt == wl.I8 and T <= 4 else 400
     for last in (64, 1, 33):
         compare(fmt, 32 * rounds + 5, STEP[fmt] * (steps - 1) + UNIT[fmt] * last, T)
+
+
+@pytest.mark.parametrize("fmt,T,rounds,steps", [(wl.Q4, 4, 768, 1), (wl.Q4, 4, 769, 1), (wl.Q4, 8, 600, 3), (wl.Q4, 8, 600, 4),
+                                                (wl.I8, 4, 704, 2), (wl.I8, 8, 600, 7), (wl.I8, 8, 600, 8), (wl.BF16, 8, 576, 1),
+                                                (wl.F16, 8, 577, 1), (wl.I8, 2, 512, 2), (wl.I8, 2, 513, 2), (wl.I8, 4, 512, 1), (wl.Q4, 2, 384, 1), (wl.Q4, 2, 385, 1)])
+def test_both_sides_of_the_rule_between_the_kernels(fmt, T, rounds, steps):
+    compare(fmt, 32 * rounds - 3, STEP[fmt] * steps - UNIT[fmt] * 5, T)
 
 
 @pytest.mark.parametrize("T", [2, 4, 8])
@@ -228,7 +235,7 @@ def test_small_results(fmt, T, M):
 
 
 @pytest.mark.parametrize("fmt", [wl.Q4, wl.I8])
-@pytest.mark.parametrize("T,M", [(2, 40), (4, 40), (8, 40), (4, 32 * 520), (8, 32 * 400)])
+@pytest.mark.parametrize("T,M", [(2, 40), (4, 40), (8, 40), (4, 32 * 710), (8, 32 * 400)])
 def test_activations_that_are_not_finite(fmt, T, M):
     """An infinity or NaN among the activations of one token makes that token's outputs NaN (an infinity meets
     the decoders' offset terms too), single and in a column, and touches no other token; activations at
