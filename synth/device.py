@@ -203,7 +203,9 @@ class SweepInputs:
                     nbytes += [m.M * m.K, m.M * 2]
                 else:
                     nbytes += [m.M * m.K * 2]
-            self.arena = torch.empty(sum(-(-n // align) * align for n in nbytes), dtype=torch.uint8, device="cuda")
+            total = sum(-(-n // align) * align for n in nbytes)
+            room = torch.empty(total + align, dtype=torch.uint8, device="cuda")   # the allocator may hand out part of a block
+            self.arena = room[-room.data_ptr() % align:][:total]
             cursor = [0]
 
             def empty(n, dtype, device):
