@@ -471,14 +471,15 @@ static hipError_t launch_short_blocks(const DevMat* htab, int nmat, int32_t toke
     return hipGetLastError();
 }
 
-/* Launches of few waves over long rows are bound by the latency of a wave's own steps and by the loads a CU
-   keeps in flight: their waves go to CUs of their own, in blocks of one, with longer steps (16-bit) or the
-   pipelined loop (int8).  us, blocks of four and of one: bf16 64 x 28672 10.0 and 7.7, 512 x 14336 6.5
-   and 6.3, 17 x 28672 beside 625 x 10496 11.2 and 8.8, but 768 x 14336 6.8 and 7.1, 1024 x 14336 7.2
-   and 7.9, 8192 x 2048 6.7 and 7.2, and rows of 4,096 alike; int8 1024 x 14336 12.5 and 6.6, 4096 x
-   8192 10.5 and 7.8, but 8192 x 14336 19.6 and 20.1, 8192 x 2064 6.0 and 6.5.  q4, two sets of loads in
-   flight in any case, takes blocks of one for all: 8192 x 8192 11.0 and 9.0, 4096 x 4096 4.6 and 4.5,
-   4096 x 28672 12.8 and 13.1, a model 1,024 wide as a chain 135 and 133. */
+/* Launches of few 16-bit or int8 waves over long rows are bound by the latency of a wave's own steps and by
+   the loads a CU keeps in flight: their waves go to CUs of their own, in blocks of one, with longer
+   steps (16-bit) or the pipelined loop (int8).  us, blocks of four and of one: bf16 64 x 28672 10.0 and
+   7.7, 512 x 14336 6.5 and 6.3, 17 x 28672 beside 625 x 10496 11.2 and 8.8, but 768 x 14336 6.8 and 7.1,
+   1024 x 14336 7.2 and 7.9, 8192 x 2048 6.7 and 7.2, and rows of 4,096 alike; int8 1024 x 14336 12.5
+   and 6.6, 4096 x 8192 10.5 and 7.8, but 8192 x 14336 19.6 and 20.1, 8192 x 2064 6.0 and 6.5.  q4, two
+   sets of loads in flight in any case, takes blocks of one (8192 x 8192 11.0 and 9.0, 28672 x 4096 14.6
+   and 13.6; a 5,120-wide model's layers as a chain 335 and 309) but for long rows of at most a wave per
+   SIMD: the 8B model as a chain, with 4096 x 14336 matrices in it, 1,131 and 1,135, and so 1,100. */
 static bool short_few(const DevMat* htab, int nmat, int rows, int64_t nc_over, int64_t most_long, int64_t most) {
     int64_t waves = 0, of_long = 0;
     for (int i = 0; i < nmat; ++i) {
@@ -491,7 +492,9 @@ static bool short_few(const DevMat* htab, int nmat, int rows, int64_t nc_over, i
 
 template <int FMT>
 static hipError_t launch_short(const DevMat* htab, int nmat, int32_t token, hipStream_t s) {
-    if constexpr (FMT == FMT_Q4) return launch_short_blocks<FMT, 4, 1, 1>(htab, nmat, token, s);
+    if constexpr (FMT == FMT_Q4)
+        return short_few(htab, nmat, 4, 256, 1024, 1024) ? launch_short_blocks<FMT, 4, 1, WAVES_PER_BLOCK>(htab, nmat, token, s)
+                                                         : launch_short_blocks<FMT, 4, 1, 1>(htab, nmat, token, s);
     else if constexpr (FMT == FMT_I8)
         return short_few(htab, nmat, 2, 256, 2048, 4096) ? launch_short_blocks<FMT, 2, 1, 1>(htab, nmat, token, s)
                                                    : launch_short_blocks<FMT, 2, 1, WAVES_PER_BLOCK>(htab, nmat, token, s);

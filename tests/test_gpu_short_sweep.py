@@ -28,7 +28,8 @@ def test_more_empty_rows_than_a_grid_of_row_groups_holds(fmt, M):
 
 @pytest.mark.parametrize("fmt,M,K", [(wsr.WSR_BF16, 768, 4104), (wsr.WSR_BF16, 769, 4104), (wsr.WSR_F16, 512, 4096),
                                      (wsr.WSR_F16, 3, 28680), (wsr.WSR_I8, 4096, 4112), (wsr.WSR_I8, 4097, 4112),
-                                     (wsr.WSR_I8, 4096, 4096), (wsr.WSR_I8, 5, 28672), (wsr.WSR_I8, 1, 5136), (wsr.WSR_Q4, 7, 28672),
+                                     (wsr.WSR_I8, 4096, 4096), (wsr.WSR_I8, 5, 28672), (wsr.WSR_I8, 1, 5136), (wsr.WSR_Q4, 7, 28672), (wsr.WSR_Q4, 4096, 8224),
+                                     (wsr.WSR_Q4, 4097, 8224),
                                      (wsr.WSR_Q4, 4099, 544)])
 def test_blocks_of_one_wave_and_of_four(fmt, M, K):
     """Both sides of the rule that gives long rows of few waves a block for each, alone and beside short rows:
