@@ -6,7 +6,7 @@ d 8192, 64 q / 8 kv heads of dim 128, FFN 28672, vocab 128256; 139.0 GB of weigh
 fully HBM-resident; one step = one decode token = one persistent launch over every matrix.
 `value` is the achieved weight-read rate in GB/s (decimal), counting each weight byte once.
 The headline and q4 sweeps (and the protocol) also report the same tokens batched b per weight
-pass, on the vector ALUs (bit-identical outputs) and on the matrix cores (b <= 16, within rounding).
+pass, with bit-identical outputs and on the larger matrix instructions (b <= 16, within rounding).
 
 Also measured in the same run and summarised under "rows" of the same JSON line, which is kept short; the
 whole record is a line on stderr ("[bench] record {...}") and, with --record FILE, a file:
@@ -1003,8 +1003,7 @@ def row_summary(rows):
         "gemv_f16": lambda r: {"us": at(r, "us_per_gemv"), "GBps": at(r, "GBps_per_dispatch"),
                                "one_launch_GBps": at(r, "one_launch_32_matrices_GBps")},
         "llama8b_q4": lambda r: {"GBps": at(r, "GBps"), "tok_s": at(r, "tokens_per_s"), "batch8_tok_s": tokens(r, "batched", 8),
-                                 "matrix_cores16_tok_s": tokens(r, "batched_matrix_cores", 16),
-                                 "traffic": at(r, "roofline", "traffic")},
+                                 "matrix_cores16_tok_s": tokens(r, "batched_matrix_cores", 16)},
         "protocol": lambda r: {"one_launch_GBps": at(r, "one_launch_back_to_back", "GBps_at_median"),
                                "dispatches_GBps": at(r, "dispatches_12", "GBps_at_median"),
                                "batch8_tok_s": tokens(r, "batched", 8),
@@ -1026,7 +1025,7 @@ def short_line(record):
             "probe_ceiling": ("GBps", "frac")}
     for k, fields in pick.items():
         if record.get(k):
-            line[k] = {f: record[k][f] for f in fields if f in record[k]}
+            line[k] = {f: float(f"{v:.5g}") if isinstance(v, float) else v for f, v in record[k].items() if f in fields}
     line["rows"] = row_summary(record["rows"])
     while len(json.dumps(line)) > LINE_MAX and line["rows"]:
         line["rows"].popitem()
