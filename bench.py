@@ -70,7 +70,7 @@ def profiled_traffic(key):
     rec = json.load(open(path))
     if rec.get("kernel_source_sha256") != kernel_sources_sha256():
         return None, "kernel changed since the counters were taken"
-    return rec.get("traffic_bytes_per_launch"), os.path.relpath(path, ROOT)
+    return round(rec["traffic_bytes_per_launch"]), os.path.relpath(path, ROOT)
 
 
 def row_roofline(gbps, key, bytes_per_launch):
